@@ -56,7 +56,7 @@ void free_layer(pp_layer *L) {
     void *bufs[] = {L->Wr,     L->bias,  L->Wgu,     L->Wd,    L->bfc,   L->bproj, L->gpart, L->counters,
                     L->selmask, L->gsig, L->idx_tmp, L->cnt_tmp, L->abpart, L->h_hi,
                     L->h_lo,   L->ypart, L->ecount,  L->tokl,  L->plan,  L->dec_tok,
-                    L->pf_cut, L->pf_ebase,
+                    L->pf_cut, L->pf_ebase, L->pair_tok,
                     L->emask};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
@@ -199,11 +199,11 @@ pp_status create_layer(pp_layer **out, int32_t d, int32_t d_ff, int32_t E, int32
     chk(dev_alloc(&L->abpart, kAbPartRows * 256));
     chk(dev_alloc(&L->h_hi, L->max_pairs * kExpertWidth));
     chk(dev_alloc(&L->h_lo, L->max_pairs * kExpertWidth));
+    chk(dev_alloc(&L->pair_tok, L->max_pairs));
     chk(dev_alloc(&L->ypart, (size_t)kDecodeChunks * kDecodeTile * d));
     chk(dev_alloc(&L->ecount, (size_t)E));
     chk(dev_alloc(&L->tokl, (size_t)E * max_tokens));
-    L->pf_ncut = (max_tokens + kPfChunk - 1) / kPfChunk + 1;
-    chk(dev_alloc(&L->pf_cut, (size_t)E * L->pf_ncut));
+    chk(dev_alloc(&L->pf_cut, (size_t)E * (pf_max_chunks(max_tokens, L->num_cu) + 1)));
     chk(dev_alloc(&L->pf_ebase, (size_t)E));
     chk(dev_alloc(&L->plan, (size_t)4 + 4 * (size_t)plan_max_groups(L->dm, max_tokens) + E + 1));
     chk(dev_alloc(&L->dec_tok, (size_t)kDecodeTile * E));

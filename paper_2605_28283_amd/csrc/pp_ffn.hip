@@ -9,16 +9,17 @@
 //
 //   dispatch_k  : per expert, the ascending list of tokens that kept it
 //                 (ballot prefix over blocks of 256 tokens + scatter), where
-//                 each chunk of kPfChunk tokens starts in it, and the plan,
+//                 each token chunk starts in it, and the plan,
 //                 written by the last expert to finish.
 //   gateup_pf_k : unit = one group, all of K, one workgroup per CU; the
 //                 gate/up projections and the SiLU product (bf16 MFMA, each
 //                 weight fragment read once per group).  The groups of a last,
 //                 partial round are split along K into pieces whose partial
 //                 sums the last piece adds in piece order.
-//   down_rows_k : unit = (R rows of d, chunk of kPfChunk tokens); the chunk's
-//                 y rows are summed in LDS over the experts in ascending
-//                 order and written once -- no float atomics, deterministic.
+//   down_rows_k : unit = (128 rows of d, a chunk of up to kPfChunk tokens);
+//                 the chunk's y rows are summed in LDS over the experts in
+//                 ascending order and written once -- no float atomics in
+//                 memory, deterministic.
 // Units sharing weights (an expert's groups; a row block's token chunks) are
 // placed on one XCD, where they meet in L2.
 #include "pp_gateup.h"
@@ -33,11 +34,10 @@ struct DNParams {
     const uint16_t *h_lo;
     float *y;
     const float *bproj;    // [d] output bias, or NULL (0)
-    const int32_t *cut;    // [E][ncut]: expert e's tokens below token c * kPfChunk
-    int ncut;
+    const int32_t *cut;    // [E][nC + 1]: expert e's tokens below token c * C
+    int C, nC;             // tokens per chunk, chunks
     const int32_t *ebase;  // [E] first pair (h row) of each expert's bucket
-    int tstride;           // toklist row stride per expert
-    PlanView plan;
+    const int32_t *pair_tok;  // [pairs] token of each h row
 };
 
 // Gate/up of one group (one expert, up to kPfGroupTokens of its tokens) in
@@ -163,7 +163,11 @@ __global__ __launch_bounds__(kGuThreads, 1) void gateup_pf_k(GUParams P) {
             e = P.plan.grp_e[g];
             n = P.plan.grp_n[g];
             p0 = P.plan.grp_pair[g];
-            if (tid < n) stok[tid] = P.plan.toklist[P.plan.grp_tok[g] + tid];
+            if (tid < n) {
+                const int t = P.plan.toklist[P.plan.grp_tok[g] + tid];
+                stok[tid] = t;
+                if (piece == 0) P.pair_tok[p0 + tid] = t;
+            }
         }
         __syncthreads();
         const int nt = (n + 15) >> 4;
@@ -303,10 +307,12 @@ __global__ __launch_bounds__(kGuThreads, 1) void gateup_pf_k(GUParams P) {
 __global__ __launch_bounds__(256) void dispatch_k(const uint32_t *__restrict__ selmask, int T,
                                                   int E, int32_t *__restrict__ ecount,
                                                   int32_t *__restrict__ tokl, int stride,
-                                                  int32_t *__restrict__ cut, int ncut,
+                                                  int32_t *__restrict__ cut, PfChunks ck,
                                                   int32_t *__restrict__ ebase, uint32_t *cnt,
                                                   PlanView plan, int num_cu) {
-    static_assert(kPfChunk % 256 == 0, "chunk starts fall on blocks of 256 tokens");
+    const int ncut = ck.n + 1;
+    // t / C for t < 2^20 and C <= 256 (the quotient's error stays below 1 / C)
+    const uint32_t rcpC = 0xFFFFFFFFu / (uint32_t)ck.C + 1u;
     constexpr int kBlocks = 8;  // blocks of 256 tokens whose flags are loaded at once
     __shared__ int scan[8];
     __shared__ __align__(16) int wc[2][kBlocks][4];  // per block and wavefront: tokens that kept e
@@ -335,15 +341,15 @@ __global__ __launch_bounds__(256) void dispatch_k(const uint32_t *__restrict__ s
             const int t = T0 + 256 * j + tid;
             const int4 c = *reinterpret_cast<const int4 *>(wc[par][j]);
             const int before = (wv > 0 ? c.x : 0) + (wv > 1 ? c.y : 0) + (wv > 2 ? c.z : 0);
-            if (tid == 0 && T0 + 256 * j < T && (T0 + 256 * j) % kPfChunk == 0)
-                cut[(size_t)e * ncut + (T0 + 256 * j) / kPfChunk] = base;
-            if ((bal[j] >> lane) & 1ull)
-                tokl[(size_t)e * stride + base + before + __popcll(bal[j] & below)] = t;
+            const int pos = base + before + __popcll(bal[j] & below);
+            const int ch = (int)__umulhi((uint32_t)t, rcpC);
+            if (t < T && ch * ck.C == t) cut[(size_t)e * ncut + ch] = pos;
+            if ((bal[j] >> lane) & 1ull) tokl[(size_t)e * stride + pos] = t;
             base += (c.x + c.y) + (c.z + c.w);
         }
     }
     if (tid == 0) {
-        cut[(size_t)e * ncut + (T + kPfChunk - 1) / kPfChunk] = base;
+        cut[(size_t)e * ncut + ck.n] = base;
         st_dev_u32(reinterpret_cast<uint32_t *>(ecount + e), (uint32_t)base);
     }
     if (!arrive_last(cnt, (unsigned)E, &s_flag)) return;
@@ -386,223 +392,324 @@ __global__ __launch_bounds__(256) void dispatch_k(const uint32_t *__restrict__ s
     }
 }
 
-// Unit = (R rows of d, a chunk of kPfChunk consecutive tokens).  The chunk's
+// Unit = (kRowBlock rows of d, a chunk of C consecutive tokens).  The chunk's
 // outputs in those rows stay in LDS for the whole unit, starting from the
 // output bias (or 0).  The experts are taken in ascending order; the tokens
 // of the chunk that kept expert e are a contiguous run of its ascending
 // bucket (positions cut[e][c] .. cut[e][c + 1]), so their h rows are
-// consecutive.  A step is one expert's R x 128 down block, staged in LDS, and
-// up to eight 16-token tiles of its run, one per wavefront (bf16 MFMA
-// 16x16x32: A = the down block, B = the tokens' h, hi then lo per K-step);
-// each tile is added to its tokens' LDS rows, and barriers separate the
-// steps.  Every output is thus the bias plus its token's pair contributions
-// in ascending expert order -- deterministic, with no atomics and no per-pair
-// rows in memory.  Every step issues the same loads (bounds-checked buffer
-// loads: lanes past the run read zeros without touching memory), kRowAhead
-// steps ahead, so each wait is for one step's data only.  The token chunks of
-// one row block are neighbouring units, placed on one XCD, so they share the
-// down blocks in L2.
-constexpr int kRowAhead = 3;  // steps whose loads are in flight
+// consecutive.  A step is one 16-token tile of a run.  Wavefronts 0 - 3 each
+// own 32 rows of the block for every token: they multiply the tile's h
+// (bf16 MFMA 16x16x32, A = the tokens' h, hi then lo per K-step, B = the
+// expert's down rows, held in registers and loaded two experts ahead) and add
+// the products to the tokens' LDS rows.  No other wavefront touches those
+// rows, so the experts' order is the wavefront's own program order: every
+// output is the bias plus its token's pair contributions in ascending expert
+// order, deterministic, with no atomics in memory and no per-pair rows.
+// Wavefronts 4 - 7 carry the h tiles from memory through registers (loads
+// kTileAhead steps ahead, which covers the Infinity Cache's latency) into one
+// of two LDS slots; one barrier per step hands a slot over.
+//
+// What bounds it: the CU's LDS accesses (per step 32 KiB of h read by the four
+// wavefronts, 8 KiB read and written of y, 8 KiB of h written: about 480
+// cycles of 650; the products take 300, and without the weight loads a step
+// is a fifth shorter).  A block of 64 rows by 512 tokens, staged in LDS and
+// multiplied by whichever wavefronts the run's tiles fill, with two barriers
+// per expert, took (LLaMA-3-8B shape) 132 us for 2048 tokens at tau 0.7 and
+// 1550 us for 16384 at tau 0.9; this takes 98 and 1110.  For 777 tokens of a
+// 1024-wide GELU layer (16-row blocks before): 51 and 23.
+constexpr int kTileAhead = 8;      // tiles in flight per carrying wavefront
+constexpr int kWAhead = 2;         // experts whose down rows are loaded ahead
+constexpr int kRowThreads = 512;
+static_assert(kTileAhead % 2 == 0, "tile k lies in slot k % 2");
 
+// Rows of the LDS outputs: token t's kRowBlock values from t * kRowBlock on,
+// each wavefront's 32 with rows r and r + 16 side by side (value 2 (r % 16) +
+// r / 16).  A lane's products with its two row tiles then make one 8-byte
+// access, and the 16 lanes of a token cover all banks once, whatever the
+// tokens.
+__device__ __forceinline__ int row_off(int t) { return t * (kRowBlock * 4); }
 
-template <int R>
 struct DownRowsLds {
-    float y[kPfChunk * (R + 4)];  // [token][row], rows padded by 4 floats
-    u32x4_t w[R / 16 * 4 * 64];   // [row tile][K-step][lane]: A fragments
-    int4 ent[kMaxExperts];        // experts with tokens in the chunk, ascending:
-                                  // (expert, tokens in the run, first pair (h row)
-                                  // of the run, its first bucket position)
-    int m, steps;
+    uint4 h[2][2][4][64];      // [slot][hi, lo][K-step][lane]: A fragments
+    int off[2][16];            // [slot][place]: the token's row_off
+    uint16_t ent[kMaxExperts]; // experts with tokens in the chunk, ascending: e | tiles << 8
+    int scan[2 * (kRowThreads / 64)];
+    // followed by the tile list, one word per tile in order (first pair (h
+    // row) | (tokens - 1) << 24), and the outputs y, whose last row (C) takes
+    // the products of empty tile places
+};
+static_assert(sizeof(DownRowsLds) % 16 == 0, "y rows are read as float4");
+static_assert(sizeof(DownRowsLds) <= kRowLdsFixed, "pf_max_chunk counts on it");
+
+// A tile's fragments as held by a multiplying wavefront.
+struct RowTile {
+    uint4 hi[4], lo[4];
+    int4 off;  // the lane's four tokens (places 4 (lane / 16) + i)
 };
 
-// One step's loads as held by a thread, with the step's (wavefront-uniform)
-// description: list entry k (m past the list), tokens n of its run and the
-// first place t16 of the wavefront's tile in the run.
-struct RowStep {
-    u32x4_t w0, w1;         // its share of the down block (R = 64: both)
-    u32x4_t bh[4], bl[4];   // the wavefront's tile: h hi / lo B fragments
-    unsigned tok;           // token of the lane's slot (0 past the run)
-    int k, n, t16;
-};
-
-// Steps in order: list entry k, round r (tiles 8 r .. 8 r + 7 of its run).
-// The cursor carries its entry and the next one (read one step ahead), so
-// moving on needs no LDS round trip.
-struct RowCursor {
-    int k, r;
-    int4 cur, next;
-};
-
-template <int R>
-__device__ __forceinline__ void rows_next(RowCursor &c, const DownRowsLds<R> &S, int m) {
-    if (c.k < m && 8 * 16 * (c.r + 1) < c.cur.y) {
-        ++c.r;
-    } else {
-        ++c.k;
-        c.r = 0;
-        c.cur = c.next;
-        c.next = S.ent[min(c.k + 1, m - 1)];
-    }
-}
-
-// Issues step c's loads (past the list: all out of range, zeros).
-template <int R>
-__device__ __forceinline__ void rows_issue(RowStep &st, const DNParams &P, const RowCursor &c,
-                                           int m, int rb, int tid) {
-    constexpr int MT = R / 16, WN = MT * 4 * 64;
-    static_assert(WN <= 2 * 512, "at most two uint4 of a down block per thread");
-    // every descriptor operand is wavefront-uniform, so it lives in SGPRs
-    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ck = __builtin_amdgcn_readfirstlane(c.k), cr = __builtin_amdgcn_readfirstlane(c.r);
-    const bool live = ck < m;
-    const int e = __builtin_amdgcn_readfirstlane(c.cur.x);
-    const int n = live ? __builtin_amdgcn_readfirstlane(c.cur.y) : 0;
-    const int p0 = __builtin_amdgcn_readfirstlane(c.cur.z);
-    const int a0 = __builtin_amdgcn_readfirstlane(c.cur.w);
-    const int t16 = 16 * (wv + 8 * cr);       // the tile's first place in the run
-    const int nt = max(0, min(16, n - t16));  // tokens in the tile
-    st.k = live ? ck : m;
-    st.n = n;
-    st.t16 = t16;
-    // down block: contiguous WN uint4
-    const auto rw = buf_rsrc(P.Wd + ((size_t)e * (P.d / 16) + (size_t)rb * MT) * 256 * 8,
-                              live ? WN * 16u : 0u);
-    st.w0 = __builtin_amdgcn_raw_buffer_load_b128(rw, (unsigned)tid * 16u, 0, 0);
-    if (WN > 512) st.w1 = __builtin_amdgcn_raw_buffer_load_b128(rw, (unsigned)(512 + tid) * 16u, 0, 0);
-    // the tile's h rows and tokens
-    const size_t q0 = (size_t)p0 + t16;
-    const auto rh = buf_rsrc(P.h_hi + q0 * kExpertWidth, (unsigned)nt * kExpertWidth * 2u);
-    const auto rl = buf_rsrc(P.h_lo + q0 * kExpertWidth, (unsigned)nt * kExpertWidth * 2u);
-    const unsigned o = ((unsigned)(lane & 15) * kExpertWidth + 8u * (lane >> 4)) * 2u;
+__device__ __forceinline__ void rows_read(RowTile &t, const DownRowsLds &S, int slot, int lane) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-        st.bh[s] = __builtin_amdgcn_raw_buffer_load_b128(rh, o + s * kKStep * 2u, 0, 0);
-        st.bl[s] = __builtin_amdgcn_raw_buffer_load_b128(rl, o + s * kKStep * 2u, 0, 0);
+        t.hi[s] = S.h[slot][0][s][lane];
+        t.lo[s] = S.h[slot][1][s][lane];
     }
-    const auto rt = buf_rsrc(P.plan.toklist + (size_t)e * P.tstride + a0 + t16, (unsigned)nt * 4u);
-    st.tok = __builtin_amdgcn_raw_buffer_load_b32(rt, (unsigned)(lane & 15) * 4u, 0, 0);
+    t.off = *reinterpret_cast<const int4 *>(&S.off[slot][4 * (lane >> 4)]);
 }
 
-// Runs step st: its down block to LDS, then the wavefront's tile.
-template <int R>
-__device__ __forceinline__ void rows_run(DownRowsLds<R> &S, const RowStep &st, int m, int t0,
-                                         int tid) {
-    constexpr int MT = R / 16, YS = R + 4, WN = MT * 4 * 64;
-    const int lane = tid & 63;
-    __syncthreads();  // the previous step's block and rows are done with
-    if (WN >= 512 || tid < WN) S.w[tid] = st.w0;
-    if (WN > 512) S.w[512 + tid] = st.w1;
-    __syncthreads();
-    const int k = __builtin_amdgcn_readfirstlane(st.k), n = __builtin_amdgcn_readfirstlane(st.n);
-    const int t16 = __builtin_amdgcn_readfirstlane(st.t16);
-    if (k >= m || t16 >= n) return;
-    // lane: rows 4 (lane / 16) + i of each row tile, its slot's token.  The
-    // rows and all of the down block's fragments are read from LDS first (the
-    // barrier ordered the reads after the previous step's adds), then the
-    // products run back to back.
-    const bool own = t16 + (lane & 15) < n;
-    float *yr = &S.y[(own ? (int)st.tok - t0 : 0) * YS + 4 * (lane >> 4)];
-    float4 yv[MT];
-    uint4 a[MT][4];
+// A tile's products on their way to the LDS outputs.
+struct RowSums {
+    f32x4 a0, a1;
+    int off[4];
+};
+
+__device__ __forceinline__ float2 sums_load(const char *yb, const RowSums &p, int i) {
+    return *reinterpret_cast<const float2 *>(yb + p.off[i]);
+}
+
+// (read, add, write: an LDS float atomic took ten times as long)
+__device__ __forceinline__ void sums_store(char *yb, float2 y, const RowSums &p, int i) {
+    *reinterpret_cast<float2 *>(yb + p.off[i]) = make_float2(y.x + p.a0[i], y.y + p.a1[i]);
+}
+
+// One step of a multiplying wavefront: multiplies tile k, adds tile k - 1's
+// products to its tokens' rows and fetches tile k + 1.  An LDS access holds up
+// the wavefront's next instruction for longer than a product does, so the 17
+// accesses are spread between the 16 products (left in a row before them,
+// they added a third to the step).  So are the loads (LOAD) of a coming
+// expert's down rows, from wn.
+template <bool LOAD>
+__device__ __forceinline__ void rows_step(const DownRowsLds &S, char *yb, const RowTile &cur,
+                                          RowTile &nxt, RowSums &prev, int slot,
+                                          const uint4 (&W)[8], int col, int lane, uint4 (&Wn)[8],
+                                          const uint16_t *wn) {
+    f32x4 a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    float2 y[4];
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-            a[mt][s] = *reinterpret_cast<const uint4 *>(&S.w[(mt * 4 + s) * 64 + lane]);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) yv[mt] = *reinterpret_cast<const float4 *>(yr + 16 * mt);
-    __builtin_amdgcn_sched_barrier(0);
-    f32x4 acc[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const uint4 bh = *reinterpret_cast<const uint4 *>(&st.bh[s]);
-        const uint4 bl = *reinterpret_cast<const uint4 *>(&st.bl[s]);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            acc[mt] = mfma16(a[mt][s], bh, acc[mt]);
-            acc[mt] = mfma16(a[mt][s], bl, acc[mt]);
+    for (int j = 0; j < 16; ++j) {
+        const int s = j >> 2;
+        a[j & 1] = mfma16((j & 2) ? cur.lo[s] : cur.hi[s], W[4 * (j & 1) + s], a[j & 1]);
+        if (j < 4) y[j] = sums_load(yb, prev, j);
+        // Tile k + 1 is in its slot, and this wavefront has read all of tile k:
+        // LDS accesses end in order, and the only ones issued since are the
+        // eight of y (7 still in flight would leave one to spare).  They are
+        // not waited for.
+        if (j == 5) asm volatile("s_waitcnt lgkmcnt(6)\n\ts_barrier" ::: "memory");
+        if (j >= 6 && j < 10) {
+            nxt.hi[j - 6] = S.h[slot][0][j - 6][lane];
+            nxt.lo[j - 6] = S.h[slot][1][j - 6][lane];
         }
+        if (j == 10) nxt.off = *reinterpret_cast<const int4 *>(&S.off[slot][4 * (lane >> 4)]);
+        if (LOAD && (j & 1)) Wn[j >> 1] = ldg16(wn + (j >> 1) * 512);
+        if (j >= 11 && j < 15) sums_store(yb, y[j - 11], prev, j - 11);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    if (own) {
+    prev.a0 = a[0];
+    prev.a1 = a[1];
+    prev.off[0] = cur.off.x + col;
+    prev.off[1] = cur.off.y + col;
+    prev.off[2] = cur.off.z + col;
+    prev.off[3] = cur.off.w + col;
+}
+
+// One expert's run of `tiles` tiles on a multiplying wavefront; k: index of
+// its first tile, whose fragments are in A; leaves the next run's first tile
+// in A.  Loads a coming expert's down rows into Wn on the way.
+__device__ __forceinline__ void rows_expert(const DownRowsLds &S, char *yb, RowTile &A, RowTile &B,
+                                            RowSums &prev, int k, int tiles, const uint4 (&W)[8],
+                                            int col, int lane, uint4 (&Wn)[8],
+                                            const uint16_t *wn) {
+    rows_step<true>(S, yb, A, B, prev, (k + 1) & 1, W, col, lane, Wn, wn);
+    for (; tiles > 2; tiles -= 2) {
+        rows_step<false>(S, yb, B, A, prev, k & 1, W, col, lane, Wn, wn);
+        rows_step<false>(S, yb, A, B, prev, (k + 1) & 1, W, col, lane, Wn, wn);
+    }
+    if (tiles == 2)
+        rows_step<false>(S, yb, B, A, prev, k & 1, W, col, lane, Wn, wn);
+    else
+        A = B;
+}
+
+// A tile on its way through a carrying wavefront's registers.  The wavefront
+// carries hi or lo (src) in two of the four K-steps, 128 consecutive bytes of
+// each row; places past the run repeat its last row.
+struct Carry {
+    u32x4_t v[2];
+    int tok, last;  // last: the tile's last place with a token
+};
+
+// d: the tile's list word; col: byte offset of the lane's first 16 bytes in
+// its row
+__device__ __forceinline__ void carry_issue(Carry &c, unsigned d, const uint16_t *src,
+                                            const int32_t *pair_tok, unsigned col, int lane) {
+    c.last = (int)(d >> 24);
+    const size_t r0 = d & 0xFFFFFFu;
+    const unsigned q = (unsigned)min(lane & 15, c.last);
+    const char *row = reinterpret_cast<const char *>(src + r0 * kExpertWidth);
+    const unsigned o = q * (kExpertWidth * 2u) + col;
+    c.v[0] = *reinterpret_cast<const u32x4_t *>(row + o);
+    c.v[1] = *reinterpret_cast<const u32x4_t *>(row + o + kKStep * 2);
+    c.tok = *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(pair_tok + r0) +
+                                               4u * q);
+}
+
+// A unit's place: the row blocks in groups of kRowGroup, a group's token
+// chunks one after another.  An XCD works on consecutive units, about 4 row
+// blocks by 8 chunks at a time: each chunk's h rows and each row block's
+// weights are then shared in its L2, and the fewest bytes come from the
+// Infinity Cache (16384 tokens of 112 experts at tau 0.9: 2.1 GB, against
+// 9.7 GB with one row block for all 32 CUs of an XCD).
+constexpr int kRowGroup = 4;
+__device__ __forceinline__ void rows_place(int unit, int nRB, int nC, int &rb, int &c) {
+    const int g = unit / (kRowGroup * nC), r = unit - g * kRowGroup * nC;
+    const int w = min(kRowGroup, nRB - g * kRowGroup);
+    c = r / w;
+    rb = g * kRowGroup + r - c * w;
+}
+
+// A multiplying wavefront's unit of m experts.  The loop ends by returning, so
+// that no path joins the loads in flight at its head and each wait covers one
+// expert's loads only.
+__device__ __forceinline__ void rows_multiply(const DownRowsLds &S, char *yb, const DNParams &P,
+                                              int C, int rb, int m, int wv, int lane) {
+    constexpr int kRing = kWAhead + 1;
+    const size_t estride = (size_t)(P.d / 16) * 4 * 512;
+    const int rt = min(rb * (kRowBlock / 16) + 2 * wv, P.d / 16 - 2);
+    const uint16_t *wd = P.Wd + (size_t)rt * 4 * 512 + lane * 8;
+    const int col = wv * 128 + (lane & 15) * 8;
+    auto ent = [&](int i) { return __builtin_amdgcn_readfirstlane((int)S.ent[min(i, m - 1)]); };
+    uint4 W[kRing][8];  // the down rows' two 16-row tiles that the wavefront owns
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            float4 v = yv[mt];
-            v.x += acc[mt][0];
-            v.y += acc[mt][1];
-            v.z += acc[mt][2];
-            v.w += acc[mt][3];
-            *reinterpret_cast<float4 *>(yr + 16 * mt) = v;
+    for (int i = 0; i < kWAhead; ++i) {
+        const uint16_t *w = wd + (size_t)(ent(i) & 255) * estride;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) W[i][j] = ldg16(w + j * 512);
+    }
+    __syncthreads();  // tile 0 is in its slot
+    RowTile A, B;
+    rows_read(A, S, 0, lane);
+    RowSums prev;
+    prev.a0 = prev.a1 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) prev.off[i] = row_off(C) + col;
+    int k = 0;
+    for (int x0 = 0;; x0 += kRing) {
+#pragma unroll
+        for (int i = 0; i < kRing; ++i) {
+            if (x0 + i >= m) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) sums_store(yb, sums_load(yb, prev, j), prev, j);
+                // the carrying wavefronts end on a whole ring
+                for (; k % kTileAhead != 0; ++k) __syncthreads();
+                return;
+            }
+            const int tiles = ent(x0 + i) >> 8;
+            rows_expert(S, yb, A, B, prev, k, tiles, W[i], col, lane, W[(i + kWAhead) % kRing],
+                        wd + (size_t)(ent(x0 + i + kWAhead) & 255) * estride);
+            k += tiles;
         }
     }
 }
 
-template <int R>
-__global__ __launch_bounds__(512, 1) void down_rows_k(DNParams P) {
-    constexpr int YS = R + 4;  // LDS row stride of y in floats
-    __shared__ DownRowsLds<R> S;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int nC = (P.T + kPfChunk - 1) / kPfChunk;
-    const int units = (P.d / R) * nC;
+// A carrying wavefront's unit (p: which of the four), in whole rings of tiles
+// with one wait each: past the last tile it carries that tile again.
+__device__ __forceinline__ void rows_carry(DownRowsLds &S, const uint32_t *list, const DNParams &P,
+                                           int C, int t0, int steps, int p, int lane) {
+    const int part = p & 1, s0 = 2 * (p >> 1);
+    const uint16_t *src = part ? P.h_lo : P.h_hi;
+    const unsigned col = (unsigned)(s0 * kKStep + 8 * (lane >> 4)) * 2u;
+    auto word = [&](int k) { return (int)list[min(k, steps - 1)]; };
+    Carry ring[kTileAhead];
+#pragma unroll
+    for (int i = 0; i < kTileAhead; ++i) {
+        carry_issue(ring[i], (unsigned)__builtin_amdgcn_readfirstlane(word(i)), src, P.pair_tok,
+                    col, lane);
+        __builtin_amdgcn_sched_barrier(0);  // issued in order: the loop's waits count on it
+    }
+    int next = word(kTileAhead);
+    for (int k0 = 0; k0 < steps; k0 += kTileAhead) {
+#pragma unroll
+        for (int i = 0; i < kTileAhead; ++i) {
+            const unsigned d = (unsigned)__builtin_amdgcn_readfirstlane(next);
+            Carry &cr = ring[i];
+            // nothing of a later tile is computed here: it would be waited for
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" : "+v"(cr.tok));
+            *reinterpret_cast<u32x4_t *>(&S.h[i % 2][part][s0][lane]) = cr.v[0];
+            *reinterpret_cast<u32x4_t *>(&S.h[i % 2][part][s0 + 1][lane]) = cr.v[1];
+            // (every 16 lanes of the four wavefronts store the same offsets)
+            const int q = lane & 15;
+            S.off[i % 2][q] = row_off(q <= cr.last ? cr.tok - t0 : C);
+            next = word(k0 + i + kTileAhead + 1);
+            carry_issue(ring[i], d, src, P.pair_tok, col, lane);
+            __syncthreads();  // tile k0 + i is in its slot; the one before has been read
+        }
+    }
+    __syncthreads();  // the last step's barrier
+}
+
+__global__ __launch_bounds__(kRowThreads, 1) void down_rows_k(DNParams P) {
+    __shared__ __align__(16) unsigned char lds[kRowLds];
+    DownRowsLds &S = *reinterpret_cast<DownRowsLds *>(lds);
+    uint32_t *list = reinterpret_cast<uint32_t *>(lds + sizeof(DownRowsLds));
+    float *y = reinterpret_cast<float *>(lds + sizeof(DownRowsLds) + pf_list_bytes(P.E, P.C));
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nC = P.nC, nRB = (P.d + kRowBlock - 1) / kRowBlock, units = nRB * nC;
     const int slots = 8 * ((units + 7) / 8);
     for (int slot = blockIdx.x; slot < slots; slot += gridDim.x) {
         const int unit = xcd_order(slot, units);
         if (unit >= units) continue;
-        const int rb = unit / nC, c = unit - rb * nC;
-        const int t0 = c * kPfChunk, nt = min(kPfChunk, P.T - t0);
-        if (wv == 0) {
-            int m = 0, steps = 0;
-            for (int e0 = 0; e0 < P.E; e0 += 64) {
-                const int e = e0 + lane;
-                int a = 0, b = 0;
-                if (e < P.E) {
-                    a = P.cut[(size_t)e * P.ncut + c];
-                    b = P.cut[(size_t)e * P.ncut + c + 1];
-                }
-                const unsigned long long bal = __ballot(b > a);
-                if (b > a)
-                    S.ent[m + __popcll(bal & ((1ull << lane) - 1ull))] =
-                        make_int4(e, b - a, P.ebase[e] + a, a);
-                m += __popcll(bal);
-                const int rounds = b > a ? (b - a + 127) / 128 : 0;
-                steps += __builtin_amdgcn_readlane(wave_scan_i32(rounds), 63);
-            }
-            if (lane == 0) {
-                S.m = m;
-                S.steps = steps;
-            }
+        int rb, c;
+        rows_place(unit, nRB, nC, rb, c);
+        const int t0 = c * P.C, nt = min(P.C, P.T - t0);
+        int n = 0, p0 = 0;  // expert tid's tokens in the chunk and their first pair
+        if (tid < P.E) {
+            const int a = P.cut[(size_t)tid * (nC + 1) + c];
+            n = P.cut[(size_t)tid * (nC + 1) + c + 1] - a;
+            p0 = P.ebase[tid] + a;
         }
-        for (int i = tid; i < nt * (R / 4); i += 512) {
-            const int t = i / (R / 4), q = i - t * (R / 4);
-            *reinterpret_cast<float4 *>(&S.y[t * YS + 4 * q]) =
-                P.bproj ? *reinterpret_cast<const float4 *>(P.bproj + rb * R + 4 * q)
-                        : make_float4(0.f, 0.f, 0.f, 0.f);
+        // a thread's values: rows r .. r + 3 and r + 16 .. r + 19.  The block's
+        // rows past d (d a multiple of 64) are computed from its last valid
+        // rows and not stored.
+        const int nr = min(kRowBlock, P.d - rb * kRowBlock);
+        constexpr int kQ = kRowBlock / 8;
+        for (int i = tid; i < nt * kQ; i += kRowThreads) {
+            const int t = i / kQ, q = i - t * kQ, r = 32 * (q >> 2) + 4 * (q & 3);
+            float4 v0 = make_float4(0.f, 0.f, 0.f, 0.f), v1 = v0;
+            if (P.bproj && r < nr) {
+                const float *b = P.bproj + rb * kRowBlock + r;
+                v0 = *reinterpret_cast<const float4 *>(b);
+                v1 = *reinterpret_cast<const float4 *>(b + 16);
+            }
+            float4 *o = reinterpret_cast<float4 *>(&y[t * kRowBlock + 8 * q]);
+            o[0] = make_float4(v0.x, v1.x, v0.y, v1.y);
+            o[1] = make_float4(v0.z, v1.z, v0.w, v1.w);
         }
+        const int tiles = (n + 15) >> 4;
+        int slot_e, slot_t, m, steps;
+        block_excl_scan2(n > 0 ? 1 : 0, tiles, &slot_e, &slot_t, &m, &steps, S.scan);
+        if (n > 0) S.ent[slot_e] = (uint16_t)(tid | (tiles << 8));
+        for (int i = 0; i < tiles; ++i)
+            list[slot_t + i] = (uint32_t)(p0 + 16 * i) | ((uint32_t)(min(16, n - 16 * i) - 1) << 24);
         __syncthreads();
-        const int m = S.m, steps = S.steps;
+        m = __builtin_amdgcn_readfirstlane(m);
+        steps = __builtin_amdgcn_readfirstlane(steps);
         if (m > 0) {
-            RowStep st[kRowAhead];
-            RowCursor ci = {0, 0, S.ent[0], S.ent[min(1, m - 1)]};  // next step to issue
-#pragma unroll
-            for (int i = 0; i < kRowAhead; ++i) {
-                rows_issue<R>(st[i], P, ci, m, rb, tid);
-                rows_next<R>(ci, S, m);
-            }
-            for (int s0 = 0; s0 < steps; s0 += kRowAhead) {
-#pragma unroll
-                for (int i = 0; i < kRowAhead; ++i) {
-                    rows_run<R>(S, st[i], m, t0, tid);
-                    rows_issue<R>(st[i], P, ci, m, rb, tid);
-                    rows_next<R>(ci, S, m);
-                }
-            }
+            if (wv < 4)
+                rows_multiply(S, reinterpret_cast<char *>(y), P, P.C, rb, m, wv, lane);
+            else
+                rows_carry(S, list, P, P.C, t0, steps, wv - 4, lane);
         }
         __syncthreads();
-        for (int i = tid; i < nt * (R / 4); i += 512) {
-            const int t = i / (R / 4), q = i - t * (R / 4);
-            *reinterpret_cast<float4 *>(P.y + (size_t)(t0 + t) * P.d + rb * R + 4 * q) =
-                *reinterpret_cast<const float4 *>(&S.y[t * YS + 4 * q]);
+        for (int i = tid; i < nt * kQ; i += kRowThreads) {
+            const int t = i / kQ, q = i - t * kQ, r = 32 * (q >> 2) + 4 * (q & 3);
+            if (r < nr) {
+                const float4 *v = reinterpret_cast<const float4 *>(&y[t * kRowBlock + 8 * q]);
+                const float4 a = v[0], b = v[1];
+                float *o = P.y + (size_t)(t0 + t) * P.d + rb * kRowBlock + r;
+                *reinterpret_cast<float4 *>(o) = make_float4(a.x, a.z, b.x, b.z);
+                *reinterpret_cast<float4 *>(o + 16) = make_float4(a.y, a.w, b.y, b.w);
+            }
         }
         __syncthreads();
     }
@@ -621,10 +728,11 @@ DNParams dn_params(pp_layer *L, int T, float *y) {
     P.y = y;
     P.bproj = L->bproj;
     P.cut = L->pf_cut;
-    P.ncut = L->pf_ncut;
+    const PfChunks ck = pf_chunks(P.d, P.E, T, L->num_cu);
+    P.C = ck.C;
+    P.nC = ck.n;
     P.ebase = L->pf_ebase;
-    P.tstride = L->max_tokens;
-    P.plan = plan_view(L, true);
+    P.pair_tok = L->pair_tok;
     return P;
 }
 
@@ -655,8 +763,8 @@ hipError_t launch_prefill_ffn(pp_layer *L, const uint16_t *x, int T, float *y, h
     const counter_layout cl = counters_for(dm, L->max_tokens);
     prof_mark(L, PP_KERNEL_DISPATCH, s, true);
     hipLaunchKernelGGL(dispatch_k, dim3(dm.E), dim3(256), 0, s, L->selmask, T, dm.E, L->ecount,
-                       L->tokl, L->max_tokens, L->pf_cut, L->pf_ncut, L->pf_ebase,
-                       L->counters + cl.dispatch_base(), plan_view(L, true), L->num_cu);
+                       L->tokl, L->max_tokens, L->pf_cut, pf_chunks(dm.d, dm.E, T, L->num_cu),
+                       L->pf_ebase, L->counters + cl.dispatch_base(), plan_view(L, true), L->num_cu);
     prof_mark(L, PP_KERNEL_DISPATCH, s, false);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
@@ -671,19 +779,8 @@ hipError_t launch_prefill_ffn(pp_layer *L, const uint16_t *x, int T, float *y, h
     err = hipGetLastError();
     if (err != hipSuccess) return err;
     const DNParams dp = dn_params(L, T, y);
-    // the widest row block (64, 32 or 16 rows) that still gives every CU a unit
-    const int nC = (T + kPfChunk - 1) / kPfChunk;
-    const int R = (dm.d / 64) * nC >= L->num_cu ? 64 : ((dm.d / 32) * nC >= L->num_cu ? 32 : 16);
-    static const int occ64 = resident(down_rows_k<64>, 512);
-    static const int occ32 = resident(down_rows_k<32>, 512);
-    static const int occ16 = resident(down_rows_k<16>, 512);
     prof_mark(L, PP_KERNEL_DOWN, s, true);
-    if (R == 64)
-        hipLaunchKernelGGL(down_rows_k<64>, dim3(occ64 * L->num_cu), dim3(512), 0, s, dp);
-    else if (R == 32)
-        hipLaunchKernelGGL(down_rows_k<32>, dim3(occ32 * L->num_cu), dim3(512), 0, s, dp);
-    else
-        hipLaunchKernelGGL(down_rows_k<16>, dim3(occ16 * L->num_cu), dim3(512), 0, s, dp);
+    hipLaunchKernelGGL(down_rows_k, dim3(L->num_cu), dim3(kRowThreads), 0, s, dp);
     prof_mark(L, PP_KERNEL_DOWN, s, false);
     return hipGetLastError();
 }

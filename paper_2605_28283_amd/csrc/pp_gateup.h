@@ -37,6 +37,7 @@ struct GUParams {
     uint32_t *cnt;
     uint16_t *h_hi;
     uint16_t *h_lo;
+    int32_t *pair_tok;  // prefill: stores the token of each h row
     // single-token decode: the kernel selects the token's experts itself from
     // the router's partial logits (rp), instead of reading the token masks
     int select_here;
@@ -377,6 +378,7 @@ inline GUParams gu_params(pp_layer *L, const uint16_t *x, int T, bool prefill) {
     P.cnt = L->counters + cl.gateup_base();
     P.h_hi = L->h_hi;
     P.h_lo = L->h_lo;
+    P.pair_tok = L->pair_tok;
     P.select_here = 0;
     return P;
 }

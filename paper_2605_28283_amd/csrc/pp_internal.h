@@ -17,7 +17,9 @@ constexpr int kDecodeTile = 64;        // tokens per decode slice (one u64 token
 constexpr int kDecodeChunks = 16;      // expert chunks of the dense-group decode down projection
 constexpr int kRouteTile = 16;         // tokens / experts per router MFMA tile
 constexpr int kMaxWidth = 8192;        // largest supported d
-constexpr int kPfChunk = 512;          // tokens per prefill down unit (their y rows stay in LDS)
+constexpr int kPfChunk = 256;          // most tokens per prefill down unit (their y rows stay in LDS)
+constexpr int kPfChunkMin = 32;        // fewest (but the last unit's)
+constexpr int kRowBlock = 128;         // rows of d per prefill down unit
 constexpr int kGroupTokens = 64;       // tokens per decode expert group (one u64 token mask)
 constexpr int kPfGroupTokens = 128;    // tokens per prefill expert group
 constexpr int kMinStepsPerSlice = 8;   // K-steps each gate/up K-slice covers at least
@@ -57,6 +59,49 @@ __host__ __device__ inline int xcd_order(int u, int n) {
     return (u % 8) * per + u / 8;
 }
 
+// Token chunks of the prefill down projection: T tokens in n chunks of C (the
+// last may be shorter).
+struct PfChunks {
+    int C, n;
+};
+
+// LDS of a prefill down unit with chunks of C tokens: h slots and tables, the
+// list of its tiles (at most ceil(C / 16) per expert, a word each) and C + 1
+// rows of outputs.
+constexpr int kRowLds = 160 * 1024;
+constexpr int kRowLdsFixed = 17088;
+__host__ __device__ inline int pf_list_bytes(int E, int C) {
+    return (E * ((C + 15) / 16) * 4 + 15) / 16 * 16;
+}
+inline int pf_row_lds(int E, int C) {
+    return kRowLdsFixed + pf_list_bytes(E, C) + (C + 1) * kRowBlock * 4;
+}
+
+// The largest chunks (256 tokens; 240 with more than about 230 experts, whose
+// tile list is longer) share each down block among the most tokens, so a call
+// takes as few rounds of (row block, chunk) units on the CUs as they give, and
+// then as many chunks as those rounds hold: a partly filled round costs as
+// much as a full one, and its units get shorter.
+inline PfChunks pf_chunks(int d, int E, int T, int num_cu) {
+    int cmax = kPfChunk;
+    while (pf_row_lds(E, cmax) > kRowLds) cmax -= 16;
+    const int nRB = (d + kRowBlock - 1) / kRowBlock;
+    const int rounds = ((T + cmax - 1) / cmax * nRB + num_cu - 1) / num_cu;
+    const int most = rounds * num_cu / nRB;  // at least ceil(T / cmax)
+    int C = (T + most - 1) / most;
+    if (C < kPfChunkMin) C = kPfChunkMin;
+    const PfChunks r = {C, (T + C - 1) / C};
+    return r;
+}
+
+// Most chunks that pf_chunks gives for up to max_tokens tokens (chunks of at
+// least 240 tokens but for the last round's).
+inline int pf_max_chunks(int max_tokens, int num_cu) {
+    const int a = (max_tokens + 239) / 240 + num_cu;
+    const int b = (max_tokens + kPfChunkMin - 1) / kPfChunkMin;
+    return a < b ? a : b;
+}
+
 // Largest number of groups a call can produce.
 inline int plan_max_groups(const pp_dims &dm, int max_tokens) {
     return dm.E + (int)(((long)max_tokens * dm.E + 63) / 64);
@@ -93,12 +138,12 @@ struct pp_layer {
     float *abpart;      // [kAbPartRows][256] K-split partial gate/up outputs
     uint16_t *h_hi;     // [pairs][128] bf16 high part of h
     uint16_t *h_lo;     // [pairs][128] bf16 low part of h (h - hi)
+    int32_t *pair_tok;  // prefill: [pairs] token of each h row
     size_t max_pairs;
     float *ypart;       // [kDecodeChunks][kDecodeTile][d] chunk partial outputs (decode, dense groups)
     int32_t *ecount;    // [E] tokens per expert (prefill)
     int32_t *tokl;      // [E][max_tokens] token ids per expert (prefill)
-    int32_t *pf_cut;    // prefill: [E][pf_ncut] bucket position where each token chunk starts
-    int pf_ncut;        // token chunks of the largest batch + 1
+    int32_t *pf_cut;    // prefill: [E][chunks + 1] bucket position where each token chunk starts
     int32_t *pf_ebase;  // prefill: [E] first pair row of each expert's bucket
     int32_t *plan;      // PlanView storage: 4 + 4 * plan_max_groups + E + 1 ints
     int32_t *dec_tok;   // [64 * E] token ids of the decode plan, pair order
