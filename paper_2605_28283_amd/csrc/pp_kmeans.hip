@@ -15,7 +15,7 @@
 //               When no cluster is over-full all hold exactly m rows, and an
 //               argmax assignment that is balanced is optimal by LP duality,
 //               whatever eps was; eps only ends price wars, so it decays
-//               geometrically (0.3 scale * 0.9^r, floor 2^-22 scale).  Small
+//               geometrically (0.05 scale * 0.9^r, floor 2^-22 scale).  Small
 //               steps cannot move a price far, so after kKmAuctionRounds
 //               rounds the rest of the excess is routed by successive
 //               shortest paths on the k-node cluster graph (edge a -> b: the
@@ -34,6 +34,8 @@
 // products exact, fp32 accumulation, HBM-bound on F), km_bid_k / km_price_k
 // (one auction round each), km_ssp_k (the shortest-path finish, one
 // workgroup), km_objective_k, km_perm_k, km_update_k.
+#include <algorithm>
+#include <cmath>
 #include <utility>
 
 #include "pp_internal.h"
@@ -45,23 +47,29 @@ constexpr int kKmMaxK = 256;
 constexpr int kKmMaxN = 65536;
 constexpr int kKmMaxD = 16384;
 constexpr int kKmCols = 64;            // columns of mu staged in LDS per chunk
-constexpr int kKmDistWaves = 8;        // km_dist_k: 8 wavefronts x 16 rows
-constexpr int kKmBidThreads = 256;
-constexpr int kKmPriceThreads = 256;
+constexpr int kKmDistWaves = 4;        // km_dist_k: 4 wavefronts x 16 rows
+constexpr int kKmBidRows = 64;         // rows per bid workgroup, one per lane
+constexpr int kKmBidWaves = 8;         // its wavefronts, each an eighth of the clusters
+constexpr int kKmPriceThreads = 1024;
 constexpr int kKmAuctionRounds = 128;  // price rounds before the shortest-path finish
+// eps of round 0, in units of the rows' mean spread of s.  From 0.3 on the
+// first 17 rounds only overshoot: 0.05 reaches the same excess that many
+// rounds earlier (14336 x 112, planted groups), 0.01 leaves price wars behind.
+constexpr double kKmEps0 = 0.05;
 constexpr int kKmBatch = 64;           // rounds enqueued between convergence checks
 constexpr int kKmSspThreads = 1024;
 
 struct KmWork {
-    float *S;            // [k][n] s_ij
+    float *S;            // [k][n] s_ij, for the bids (lanes over rows)
+    float *St;           // [n][k] the same, for the shortest-path finish (lanes over clusters)
     double *xnorm;       // [n]
-    float *list;         // [k][n] margins (rounded up to fp32) of each cluster's rows
-    int32_t *memb;       // [k][n] the rows themselves (same order as list)
+    float *margin;       // [n] best minus second-best value of each row, rounded up to fp32
+    int32_t *memb;       // [k][n] shortest-path finish: the rows of each cluster
     double *lam;         // [k] cluster prices
     double *part;        // [bid workgroups] spread sums, then [bid workgroups] = the eps scale
     float *cn;           // [k] ||mu_j||^2
     uint16_t *mu3;       // [3][k][D] bf16 parts of mu
-    int32_t *count;      // [k] rows whose argmax is j (this round)
+    int32_t *count;      // [k] shortest-path finish: rows of each cluster
     double *base;        // [k][k] shortest-path finish: min over a's rows of s_ib - s_ia
     int32_t *bidx;       // [k][k] the row attaining it (lowest index on ties)
     int32_t *pos;        // [n] a row's place in its cluster's member list
@@ -69,7 +77,7 @@ struct KmWork {
                          // [3] rounds the step took
 };
 
-inline int bid_blocks(int n) { return (n + kKmBidThreads / 4 - 1) / (kKmBidThreads / 4); }
+inline int bid_blocks(int n) { return (n + kKmBidRows - 1) / kKmBidRows; }
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -83,8 +91,9 @@ size_t km_layout(int n, int D, int k, KmWork *w, char *base) {
     };
     KmWork t;
     t.S = reinterpret_cast<float *>(take(sizeof(float) * (size_t)k * n));
+    t.St = reinterpret_cast<float *>(take(sizeof(float) * (size_t)k * n));
     t.xnorm = reinterpret_cast<double *>(take(sizeof(double) * n));
-    t.list = reinterpret_cast<float *>(take(sizeof(float) * (size_t)k * n));
+    t.margin = reinterpret_cast<float *>(take(sizeof(float) * (size_t)n));
     t.memb = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (size_t)k * n));
     t.lam = reinterpret_cast<double *>(take(sizeof(double) * k));
     t.part = reinterpret_cast<double *>(take(sizeof(double) * (bid_blocks(n) + 1)));
@@ -153,19 +162,26 @@ __global__ __launch_bounds__(256) void km_split_k(const float *__restrict__ mu, 
     if (tid == 0) cn[j] = (float)red[0];
 }
 
-// s[j][i] = ||mu_j||^2 - 2 x_i . mu_j.  A workgroup owns 128 rows (16 per
+// s[j][i] = ||mu_j||^2 - 2 x_i . mu_j.  A workgroup owns 64 rows (16 per
 // wavefront, the MFMA A operand straight from HBM, prefetched one chunk
-// ahead); the three bf16 parts of mu, kKmCols columns at a time, are staged
-// in LDS in B-operand order and shared by the 8 wavefronts.  NT = ceil(k/16)
-// cluster tiles per wavefront.
+// ahead; 14336 rows then fill 224 of the CUs); the three bf16 parts of mu,
+// kKmCols columns at a time, are staged in LDS and shared by the wavefronts.
+// A chunk is fetched into registers while the one before it is multiplied
+// (fetched behind the barrier, 128 rows a workgroup, the kernel took 257 us
+// for 14336 x 4096 x 112).  A fetch takes 128 bytes of eight rows of mu, whole
+// cache lines; 16-byte piece c of row r lies at place c ^ (r % 8), so that a
+// fragment's reads spread over all banks.  NT = ceil(k/16) cluster tiles per
+// wavefront.
 template <int NT>
-__global__ __launch_bounds__(64 * kKmDistWaves) void km_dist_k(const uint16_t *__restrict__ F,
-                                                              int n, int D, int k,
-                                                              const uint16_t *__restrict__ mu3,
-                                                              const float *__restrict__ cn,
-                                                              float *__restrict__ S) {
-    // bs[part][tile][K-step of 32][lane]: 16 bytes per lane
-    __shared__ uint4 bs[3][NT][kKmCols / 32][64];
+__global__ __launch_bounds__(64 * kKmDistWaves, 1) void km_dist_k(const uint16_t *__restrict__ F,
+                                                                 int n, int D, int k,
+                                                                 const uint16_t *__restrict__ mu3,
+                                                                 const float *__restrict__ cn,
+                                                                 float *__restrict__ S,
+                                                                 float *__restrict__ St) {
+    // bs[part][tile][8 rows][row, piece]: 16 bytes each
+    __shared__ u32x4_t bs[3][NT][2][64];
+    static_assert(kKmCols == 64, "eight 16-byte pieces per row and chunk");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int p = lane & 15, g = lane >> 4;
     const int i0 = blockIdx.x * (16 * kKmDistWaves) + wv * 16;
@@ -175,32 +191,51 @@ __global__ __launch_bounds__(64 * kKmDistWaves) void km_dist_k(const uint16_t *_
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     constexpr int kSteps = kKmCols / 32;
-    uint4 a[kSteps], an[kSteps];
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s) a[s] = ldg16(frow + 32 * s);
     const size_t plane = (size_t)k * D;
-    for (int c0 = 0; c0 < D; c0 += kKmCols) {
-        // stage mu parts for columns c0 .. c0 + kKmCols - 1
-        for (int e = tid; e < 3 * NT * kSteps * 64; e += 64 * kKmDistWaves) {
-            const int l = e & 63, s = (e >> 6) % kSteps, t = (e >> 6) / kSteps % NT,
-                      part = (e >> 6) / kSteps / NT;
-            const int j = t * 16 + (l & 15);
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (j < k) v = ldg16(mu3 + part * plane + (size_t)j * D + c0 + 32 * s + 8 * (l >> 4));
-            bs[part][t][s][l] = v;
-        }
-        if (c0 + kKmCols < D) {
+    // the workgroup's 6 NT pieces of 64 x 16 bytes of a chunk, wavefront w
+    // taking w, w + 4, ...
+    constexpr int kPieces = 6 * NT, kPer = (kPieces + kKmDistWaves - 1) / kKmDistWaves;
+    u32x4_t m[kPer];
+    auto fetch = [&](int c0) {
 #pragma unroll
-            for (int s = 0; s < kSteps; ++s) an[s] = ldg16(frow + c0 + kKmCols + 32 * s);
+        for (int u = 0; u < kPer; ++u) {
+            const int e = min(wv + u * kKmDistWaves, kPieces - 1);
+            const int part = e / (2 * NT), th = e - part * (2 * NT);
+            const int j = min(8 * th + (lane >> 3), k - 1);  // past k: columns never stored
+            m[u] = *reinterpret_cast<const u32x4_t *>(mu3 + part * plane + (size_t)j * D + c0 +
+                                                      8 * ((lane & 7) ^ (lane >> 3)));
+        }
+    };
+    u32x4_t a[kSteps];
+    fetch(0);
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) a[s] = *reinterpret_cast<const u32x4_t *>(frow + 32 * s);
+    u32x4_t *flat = &bs[0][0][0][0];
+    const int r = lane & 7;
+    for (int c0 = 0; c0 < D; c0 += kKmCols) {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int e = wv + u * kKmDistWaves;
+            if (e < kPieces) flat[e * 64 + lane] = m[u];
         }
         __syncthreads();
+        // the next chunk (the last one again at the end)
+        const int cn0 = min(c0 + kKmCols, D - kKmCols);
+        fetch(cn0);
+        u32x4_t an[kSteps];
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s)
+            an[s] = *reinterpret_cast<const u32x4_t *>(frow + cn0 + 32 * s);
 #pragma unroll
         for (int s = 0; s < kSteps; ++s)
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
                 for (int part = 0; part < 3; ++part)
-                    acc[t] = mfma16(a[s], bs[part][t][s][lane], acc[t]);
+                    acc[t] = mfma16(__builtin_bit_cast(uint4, a[s]),
+                                    __builtin_bit_cast(
+                                        uint4, bs[part][t][(lane >> 3) & 1][8 * r + ((4 * s + g) ^ r)]),
+                                    acc[t]);
         __syncthreads();
 #pragma unroll
         for (int s = 0; s < kSteps; ++s) a[s] = an[s];
@@ -214,18 +249,19 @@ __global__ __launch_bounds__(64 * kKmDistWaves) void km_dist_k(const uint16_t *_
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int i = i0 + 4 * g + q;
-            if (i < n) S[(size_t)j * n + i] = c - 2.0f * acc[t][q];
+            if (i < n) {
+                const float v = c - 2.0f * acc[t][q];
+                S[(size_t)j * n + i] = v;
+                St[(size_t)i * k + j] = v;
+            }
         }
     }
 }
 
-// Auction state for one assignment step: prices 0, counts 0, flags clear.
-__global__ void km_auction_init_k(int k, double *lam, int32_t *count, int32_t *flags) {
+// Auction state for one assignment step: prices 0, flags clear.
+__global__ void km_auction_init_k(int k, double *lam, int32_t *flags) {
     const int t = threadIdx.x;
-    for (int j = t; j < k; j += blockDim.x) {
-        lam[j] = 0.0;
-        count[j] = 0;
-    }
+    for (int j = t; j < k; j += blockDim.x) lam[j] = 0.0;
     if (t < 4) flags[t] = 0;
 }
 
@@ -249,35 +285,24 @@ __device__ __forceinline__ Best2 merge_best2(Best2 a, Best2 b) {
     a.smax = fmaxf(a.smax, b.smax);
     return a;
 }
-__device__ __forceinline__ Best2 shfl_best2(const Best2 &v, int st) {
-    Best2 o;
-    o.w1 = __shfl_xor(v.w1, st, 64);
-    o.w2 = __shfl_xor(v.w2, st, 64);
-    o.j1 = __shfl_xor(v.j1, st, 64);
-    o.smin = __shfl_xor(v.smin, st, 64);
-    o.smax = __shfl_xor(v.smax, st, 64);
-    return o;
-}
 
 // Round r, bids: every row's argmax j1 of w_ij = -s_ij - lambda_j (first
 // index on ties) and its margin w1 - w2 (w2 the best over the other
-// clusters), rounded up to fp32 and appended, with the row, to cluster j1's
-// lists; counts per cluster.  kBidLanes adjacent lanes share a row, each
-// taking every kBidLanes-th cluster with its loads 32 at a time in flight, and
-// their partial results are merged.  Exits at once when the previous round
-// left no cluster over-full (the assignment then stands).
-constexpr int kBidLanes = 4;
-constexpr int kBidRows = kKmBidThreads / kBidLanes;  // rows per workgroup
-
-__global__ __launch_bounds__(kKmBidThreads) void km_bid_k(const float *__restrict__ S, int n, int k,
-                                                          int r, KmWork W,
-                                                          int32_t *__restrict__ assign) {
-    constexpr int kBatch = 32;  // a lane's clusters in flight at once (k <= 128: all of them)
-    __shared__ double lam[kKmMaxK];
-    __shared__ int cnt[kKmMaxK];
-    __shared__ int base[kKmMaxK];
-    __shared__ double spread[kBidRows];
-    const int tid = threadIdx.x;
+// clusters), rounded up to fp32.  A lane owns a row, a wavefront an eighth of
+// the clusters (its loads 16 at a time in flight, 256 contiguous bytes each),
+// and the wavefronts' partial results are merged through LDS.  Latency-bound
+// (6.4 MB of s for 14336 x 112): the row is only written down here -- the
+// price kernel sorts the rows by cluster itself, which costs it less than
+// lists appended through device-wide counters cost this kernel (LLaMA-3-8B
+// layer, a round of both kernels: 16.6 us with the lists).  Exits at once when
+// the previous round left no cluster over-full (the assignment then stands).
+__global__ __launch_bounds__(64 * kKmBidWaves) void km_bid_k(const float *__restrict__ S, int n,
+                                                             int k, int r, KmWork W,
+                                                             int32_t *__restrict__ assign) {
+    constexpr int kBatch = 16;  // a lane's clusters in flight at once (k <= 128: all of them)
+    __shared__ Best2 part[kKmBidWaves][kKmBidRows];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (W.flags[2]) return;
     if (r > 0 && W.flags[(r - 1) & 1] == 0) {
         if (blockIdx.x == 0 && tid == 0) {
@@ -287,27 +312,27 @@ __global__ __launch_bounds__(kKmBidThreads) void km_bid_k(const float *__restric
         return;
     }
     if (blockIdx.x == 0 && tid == 0) W.flags[r & 1] = 0;
-    for (int j = tid; j < k; j += kKmBidThreads) {
-        lam[j] = W.lam[j];
-        cnt[j] = 0;
-    }
-    __syncthreads();
-    const int q = tid % kBidLanes, row = tid / kBidLanes;
-    const int i = blockIdx.x * kBidRows + row;
+    const int i = blockIdx.x * kKmBidRows + lane;
     const bool valid = i < n;
     const int ii = min(i, n - 1);
+    const int per = (k + kKmBidWaves - 1) / kKmBidWaves;
+    const int jA = wv * per, jB = min(jA + per, k);
     Best2 v{-INFINITY, -INFINITY, 0x7FFFFFFF, INFINITY, -INFINITY};
-    for (int j0 = q; j0 < k; j0 += kBatch * kBidLanes) {
+    for (int j0 = jA; j0 < jB; j0 += kBatch) {
         float sv[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u)
-            sv[u] = S[(size_t)min(j0 + u * kBidLanes, k - 1) * n + ii];
+        double lam[kBatch];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const int j = j0 + u * kBidLanes;
-            if (j < k) {
-                const double w = -(double)sv[u] - lam[j];
-                const bool b1 = w > v.w1;  // ascending j within a lane: first wins ties
+            const int j = min(j0 + u, k - 1);
+            sv[u] = S[(size_t)j * n + ii];
+            lam[u] = W.lam[j];
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int j = j0 + u;
+            if (j < jB) {
+                const double w = -(double)sv[u] - lam[u];
+                const bool b1 = w > v.w1;  // ascending j: the first wins ties
                 v.w2 = b1 ? v.w1 : fmax(v.w2, w);
                 v.w1 = b1 ? w : v.w1;
                 v.j1 = b1 ? j : v.j1;
@@ -316,168 +341,292 @@ __global__ __launch_bounds__(kKmBidThreads) void km_bid_k(const float *__restric
             }
         }
     }
+    part[wv][lane] = v;
+    __syncthreads();
+    if (wv != 0) return;
 #pragma unroll
-    for (int st = 1; st < kBidLanes; st <<= 1) v = merge_best2(v, shfl_best2(v, st));
-    const bool lead = q == 0 && valid;
-    int slot = 0;
-    if (lead) slot = atomicAdd(&cnt[v.j1], 1);
-    __syncthreads();
-    for (int j = tid; j < k; j += kKmBidThreads) base[j] = cnt[j] ? atomicAdd(&W.count[j], cnt[j]) : 0;
-    __syncthreads();
-    if (lead) {
+    for (int w = 1; w < kKmBidWaves; ++w) v = merge_best2(v, part[w][lane]);
+    if (valid) {
         const double mg = v.w1 - v.w2;  // +inf when k == 1
-        const int at = base[v.j1] + slot;
-        assign[i] = v.j1;
-        W.list[(size_t)v.j1 * n + at] = isinf(mg) ? 3.0e38f : __double2float_ru(mg);
-        W.memb[(size_t)v.j1 * n + at] = i;
-        W.pos[i] = at;
+        assign[i] = min(v.j1, k - 1);  // (NaN features choose no cluster)
+        W.margin[i] = isinf(mg) ? 3.0e38f : __double2float_ru(mg);
     }
     if (r == 0) {  // eps scale: sum of per-row spreads, fixed order
-        if (q == 0) spread[row] = valid ? (double)v.smax - (double)v.smin : 0.0;
-        __syncthreads();
-        for (int st = kBidRows / 2; st >= 1; st >>= 1) {
-            if (tid < st) spread[tid] += spread[tid + st];
-            __syncthreads();
-        }
-        if (tid == 0) W.part[blockIdx.x] = spread[0];
+        double sp = valid ? (double)v.smax - (double)v.smin : 0.0;
+#pragma unroll
+        for (int st = 32; st >= 1; st >>= 1) sp += __shfl_xor(sp, st, 64);
+        if (lane == 0) W.part[blockIdx.x] = sp;
     }
 }
 
-// Round r, prices: one workgroup per cluster.  An over-full cluster finds the
-// (m+1)-th largest margin in its list by a 4-pass radix select on the fp32
-// bits (margins are >= 0, so bit order is value order; the list order does
-// not matter) and raises its price by that margin plus eps_r; it also counts
-// itself in flags[r & 1].  A list of up to kKmPriceLds margins is copied into
-// LDS once and the passes read it there.  The eps scale (the round-0 spread
-// sums, added in workgroup order) is formed in round 0 and kept in
-// part[nbid].  Every workgroup clears its count for the next round.
-constexpr int kKmPriceLds = 16384;
+// Round r, prices: one workgroup per cluster.  It gathers the margins of its
+// rows in LDS (reading every row's cluster, 16 rows a thread at once), and an
+// over-full cluster finds the (m+1)-th largest of them by a radix select on
+// the fp32 bits in three passes of 11, 11 and 10 bits (margins are >= 0, so
+// bit order is value order; the order they were gathered in does not matter)
+// and raises its price by that margin plus eps (the round's, in units of the
+// eps scale); it also counts itself in flags[r & 1].  More than kKmPriceLds
+// rows are read again from memory by every pass.  The eps scale (the round-0
+// spread sums, in a fixed order) is formed in round 0 and kept in part[nbid].
+constexpr int kKmPriceLds = 8192;
+constexpr int kKmDigits = 2048;
 
-__global__ __launch_bounds__(kKmPriceThreads) void km_price_k(int n, int k, int m, int r,
-                                                              int nbid, KmWork W) {
-    constexpr int kBatch = 4;
-    constexpr int kCopy = 8;
-    static_assert(kKmPriceThreads == 256, "one thread per radix digit");
-    __shared__ int hist[256];
-    __shared__ int scan[8];
+__global__ __launch_bounds__(kKmPriceThreads) void km_price_k(int n, int m, int r, int nbid,
+                                                              double eps, KmWork W,
+                                                              const int32_t *__restrict__ assign) {
+    constexpr int kBatch = 16;
+    static_assert(kKmDigits == 2 * kKmPriceThreads, "two digits per thread");
+    __shared__ int hist[kKmDigits];
+    __shared__ int scan[2 * (kKmPriceThreads / 64)];
     __shared__ uint32_t s_pref;
-    __shared__ int s_rank;
+    __shared__ int s_rank, s_c;
     __shared__ uint32_t sl[kKmPriceLds];
-    const int j = blockIdx.x, tid = threadIdx.x;
-    if (W.flags[2]) return;
-    const int c = W.count[j];
-    __syncthreads();
-    if (tid == 0) W.count[j] = 0;
-    if (c <= m) return;
+    const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    auto rows = [&](int i0, int (&a)[kBatch], uint32_t (&v)[kBatch]) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int i = min(i0 + u * kKmPriceThreads + tid, n - 1);
+            a[u] = assign[i];
+            v[u] = __float_as_uint(W.margin[i]);
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            if (i0 + u * kKmPriceThreads + tid >= n) a[u] = -1;
+    };
+    const int done = W.flags[2];
+    int a[kBatch];  // the first rows' loads do not wait for the flag
+    uint32_t v[kBatch];
+    rows(0, a, v);
+    if (done) return;
     if (tid == 0) {
+        s_c = 0;
         s_pref = 0u;
         s_rank = m;  // 0-based rank from the top
     }
-    const float *lst = W.list + (size_t)j * n;
-    const bool inl = c <= kKmPriceLds;  // workgroup-uniform
-    if (inl) {
-        for (int i0 = 0; i0 < c; i0 += kCopy * kKmPriceThreads) {
-            uint32_t v[kCopy];
+    hist[tid] = 0;
+    hist[tid + kKmPriceThreads] = 0;
+    __syncthreads();
+    for (int i0 = 0;;) {
+        // one counter update per wavefront
+        unsigned long long mine[kBatch];
+        int total = 0;
 #pragma unroll
-            for (int u = 0; u < kCopy; ++u)
-                v[u] = __float_as_uint(lst[min(i0 + u * kKmPriceThreads + tid, c - 1)]);
-#pragma unroll
-            for (int u = 0; u < kCopy; ++u)
-                if (i0 + u * kKmPriceThreads + tid < c) sl[i0 + u * kKmPriceThreads + tid] = v[u];
+        for (int u = 0; u < kBatch; ++u) {
+            mine[u] = __ballot(a[u] == j);
+            total += __popcll(mine[u]);
         }
+        if (total) {
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&s_c, total);
+            at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                if (a[u] == j) {
+                    const int o = at + __popcll(mine[u] & ((1ull << lane) - 1ull));
+                    if (o < kKmPriceLds) sl[o] = v[u];
+                    atomicAdd(&hist[v[u] >> 21], 1);  // the first pass's digits
+                }
+                at += __popcll(mine[u]);
+            }
+        }
+        i0 += kBatch * kKmPriceThreads;
+        if (i0 >= n) break;
+        rows(i0, a, v);
     }
-    {
-        uint32_t mask = 0u;
-        for (int pass = 0; pass < 4; ++pass) {
-            const int shift = 24 - 8 * pass;
+    __syncthreads();
+    const int c = s_c;
+    if (c <= m) return;
+    const bool inl = c <= kKmPriceLds;  // workgroup-uniform
+    uint32_t mask = 0u;
+#pragma unroll
+    for (int pass = 0; pass < 3; ++pass) {
+        const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
+        const uint32_t digits = pass == 2 ? 1023u : 2047u;
+        if (pass > 0) {
             hist[tid] = 0;
+            hist[tid + kKmPriceThreads] = 0;
             __syncthreads();
             const uint32_t pref = s_pref;
-            for (int i0 = 0; i0 < c; i0 += kBatch * kKmPriceThreads) {
-                uint32_t v[kBatch];
-    #pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    const int ix = min(i0 + u * kKmPriceThreads + tid, c - 1);
-                    v[u] = inl ? sl[ix] : __float_as_uint(lst[ix]);
-                }
-    #pragma unroll
-                for (int u = 0; u < kBatch; ++u)
-                    if (i0 + u * kKmPriceThreads + tid < c && (v[u] & mask) == pref)
-                        atomicAdd(&hist[(v[u] >> shift) & 255], 1);
-            }
-            __syncthreads();
-            {  // digits from the top: thread t takes digit 255 - t; the selected
-               // digit is where the running count first exceeds the rank
-                const int h = hist[255 - tid], rank = s_rank;
-                int ex, ex1, tot, tot1;
-                block_excl_scan2(h, 0, &ex, &ex1, &tot, &tot1, scan);
-                __syncthreads();
-                if (ex <= rank && rank < ex + h) {
-                    s_rank = rank - ex;
-                    s_pref = pref | ((uint32_t)(255 - tid) << shift);
+            if (inl) {
+                for (int i = tid; i < c; i += kKmPriceThreads)
+                    if ((sl[i] & mask) == pref) atomicAdd(&hist[(sl[i] >> shift) & digits], 1);
+            } else {
+                for (int i0 = 0; i0 < n; i0 += kBatch * kKmPriceThreads) {
+                    rows(i0, a, v);
+#pragma unroll
+                    for (int u = 0; u < kBatch; ++u)
+                        if (a[u] == j && (v[u] & mask) == pref)
+                            atomicAdd(&hist[(v[u] >> shift) & digits], 1);
                 }
             }
-            mask |= 255u << shift;
             __syncthreads();
         }
+        // digits from the top, two to a thread; the selected digit is where
+        // the running count first exceeds the rank
+        const int d0 = kKmDigits - 1 - 2 * tid, h0 = hist[d0], h1 = hist[d0 - 1];
+        const int rank = s_rank;
+        const uint32_t pref = s_pref;
+        int ex, ex1, tot, tot1;
+        block_excl_scan2(h0 + h1, 0, &ex, &ex1, &tot, &tot1, scan);
+        if (ex <= rank && rank < ex + h0 + h1) {
+            const bool first = rank < ex + h0;
+            s_rank = rank - ex - (first ? 0 : h0);
+            s_pref = pref | ((uint32_t)(first ? d0 : d0 - 1) << shift);
+        }
+        mask |= digits << shift;
+        __syncthreads();
     }
-    if (tid == 0) {
+    if (tid < 64) {
         double scale = 0.0;
         if (r == 0) {  // every over-full cluster forms the same value
-            for (int b = 0; b < nbid; ++b) scale += W.part[b];
+            for (int b = lane; b < nbid; b += 64) scale += W.part[b];
+#pragma unroll
+            for (int st = 32; st >= 1; st >>= 1) scale += __shfl_xor(scale, st, 64);
             scale /= (double)n;
-            W.part[nbid] = scale;
+            if (lane == 0) W.part[nbid] = scale;
         } else {
             scale = W.part[nbid];
         }
-        double e = 0.3 * pow(0.9, (double)r);
-        if (e < 0x1p-22) e = 0x1p-22;
-        W.lam[j] += (double)__uint_as_float(s_pref) + e * scale;
-        atomicAdd(&W.flags[r & 1], 1);
+        if (lane == 0) {
+            W.lam[j] += (double)__uint_as_float(s_pref) + eps * scale;
+            atomicAdd(&W.flags[r & 1], 1);
+        }
     }
 }
 
-// Edge row a of the shortest-path finish: base[a][b] = min over a's rows i
-// of s_bi - s_ai and the row attaining it (lowest index on ties, so the
+// The members of every cluster after a bid round, ascending, for the
+// shortest-path finish: one workgroup per cluster.
+__global__ __launch_bounds__(1024) void km_members_k(const int32_t *__restrict__ assign, int n,
+                                                     KmWork W) {
+    __shared__ int scan[32];
+    const int j = blockIdx.x, tid = threadIdx.x;
+    int base = 0;
+    for (int i0 = 0; i0 < n; i0 += 1024) {
+        const int i = i0 + tid;
+        const int f = (i < n && assign[i] == j) ? 1 : 0;
+        int ex, ex1, tot, tot1;
+        block_excl_scan2(f, 0, &ex, &ex1, &tot, &tot1, scan);
+        if (f) {
+            W.memb[(size_t)j * n + base + ex] = i;
+            W.pos[i] = base + ex;
+        }
+        base += tot;
+    }
+    if (tid == 0) W.count[j] = base;
+}
+
+// LDS of one edge row: a batch of the cluster's rows, and the wavefronts'
+// minima.
+struct SspRowLds {
+    int row[kKmSspThreads];
+    double best[kKmSspThreads / 64][kKmMaxK / 2];
+    int bi[kKmSspThreads / 64][kKmMaxK / 2];
+};
+
+// Edge row a of the shortest-path finish: base[b] = min over a's rows i of
+// s_bi - s_ai and bidx[b] the row attaining it (lowest index on ties, so the
 // member-list order does not matter); b = a and empty clusters give +inf.
-// Wavefront w takes b = w, w + 16, ...; lanes stride over the members.
-__device__ void ssp_row(const float *__restrict__ S, int n, int k, int a, int na,
-                        const int32_t *memb, double *base, int32_t *bidx) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int b = wv; b < k; b += kKmSspThreads / 64) {
-        double best = INFINITY;
-        int bi = 0x7FFFFFFF;
-        if (b != a) {
-            for (int t = lane; t < na; t += 64) {
-                const int i = memb[(size_t)a * n + t];
-                const double v = (double)S[(size_t)b * n + i] - (double)S[(size_t)a * n + i];
-                if (v < best || (v == best && i < bi)) {
-                    best = v;
-                    bi = i;
+// Called by the whole workgroup: wavefront w takes rows w, w + 16, ..., its
+// lanes the clusters, so a row is read as its k consecutive values of St (with
+// lanes over rows instead, each value was a cache line of its own and an edge
+// row took 14 us, 128 rows of 112 clusters).
+__device__ __forceinline__ void ssp_row(const float *__restrict__ St, int n, int k, int a, int na,
+                                        const int32_t *memb, double *base, int32_t *bidx,
+                                        SspRowLds &R) {
+    constexpr int kWaves = kKmSspThreads / 64, kV = kKmMaxK / 64, kB = 8;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    double best[kV];
+    int bi[kV];
+#pragma unroll
+    for (int q = 0; q < kV; ++q) {
+        best[q] = INFINITY;
+        bi[q] = 0x7FFFFFFF;
+    }
+    for (int t0 = 0; t0 < na; t0 += kKmSspThreads) {
+        const int nt = min(kKmSspThreads, na - t0);
+        if (tid < nt) R.row[tid] = memb[(size_t)a * n + t0 + tid];
+        __syncthreads();
+        for (int u0 = wv; u0 < nt; u0 += kB * kWaves) {
+            int row[kB];
+            float own[kB], sv[kB][kV];
+#pragma unroll
+            for (int u = 0; u < kB; ++u) {
+                row[u] = R.row[min(u0 + u * kWaves, nt - 1)];  // past the batch: its last row again
+                const float *p = St + (size_t)row[u] * k;
+                own[u] = p[a];
+#pragma unroll
+                for (int q = 0; q < kV; ++q) sv[u][q] = 64 * q < k ? p[min(lane + 64 * q, k - 1)] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < kB; ++u)
+#pragma unroll
+                for (int q = 0; q < kV; ++q) {
+                    const double v = (double)sv[u][q] - (double)own[u];
+                    if (v < best[q] || (v == best[q] && row[u] < bi[q])) {
+                        best[q] = v;
+                        bi[q] = row[u];
+                    }
+                }
+        }
+        __syncthreads();
+    }
+    // the wavefronts' minima, half of the clusters at a time
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (128 * h >= k) break;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            R.best[wv][lane + 64 * q] = best[2 * h + q];
+            R.bi[wv][lane + 64 * q] = bi[2 * h + q];
+        }
+        __syncthreads();
+        const int b = 128 * h + tid;
+        if (tid < 128 && b < k) {
+            double v = R.best[0][tid];
+            int i = R.bi[0][tid];
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) {
+                const double o = R.best[w][tid];
+                const int oi = R.bi[w][tid];
+                if (o < v || (o == v && oi < i)) {
+                    v = o;
+                    i = oi;
                 }
             }
+            base[b] = b == a ? (double)INFINITY : v;
+            bidx[b] = b == a ? 0x7FFFFFFF : i;
         }
-#pragma unroll
-        for (int st = 32; st >= 1; st >>= 1) {
-            const double ov = __shfl_xor(best, st, 64);
-            const int oi = __shfl_xor(bi, st, 64);
-            if (ov < best || (ov == best && oi < bi)) {
-                best = ov;
-                bi = oi;
-            }
-        }
-        if (lane == 0) {
-            base[(size_t)a * k + b] = best;
-            bidx[(size_t)a * k + b] = bi;
-        }
+        __syncthreads();
     }
 }
 
 // All edge rows at once, one workgroup per cluster, from the member lists of
 // the bid round that precedes the finish (its argmax matches the prices).
-__global__ __launch_bounds__(kKmSspThreads) void km_ssp_rows_k(const float *__restrict__ S, int n,
-                                                               int k, KmWork W) {
-    ssp_row(S, n, k, blockIdx.x, W.count[blockIdx.x], W.memb, W.base, W.bidx);
+__global__ __launch_bounds__(kKmSspThreads) void km_ssp_rows_k(int n, int k, KmWork W) {
+    __shared__ SspRowLds R;
+    const int a = blockIdx.x;
+    ssp_row(W.St, n, k, a, W.count[a], W.memb, W.base + (size_t)a * k, W.bidx + (size_t)a * k, R);
+}
+
+// The smallest (value, index) over the wavefront, lower index on equal values.
+template <int ST>
+__device__ __forceinline__ void wave_min_step(double &d, int &v, int lane) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(d);
+    const uint32_t lo = xor_lane<ST>((uint32_t)u, lane), hi = xor_lane<ST>((uint32_t)(u >> 32), lane);
+    const double od = __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+    const int ov = (int)xor_lane<ST>((uint32_t)v, lane);
+    if (od < d || (od == d && ov < v)) {
+        d = od;
+        v = ov;
+    }
+}
+__device__ __forceinline__ void wave_min(double &d, int &v, int lane) {
+    wave_min_step<1>(d, v, lane);
+    wave_min_step<2>(d, v, lane);
+    wave_min_step<4>(d, v, lane);
+    wave_min_step<8>(d, v, lane);
+    wave_min_step<16>(d, v, lane);
+    wave_min_step<32>(d, v, lane);
 }
 
 // Shortest-path finish of an assignment step (one workgroup; every loop is
@@ -487,77 +636,99 @@ __global__ __launch_bounds__(kKmSspThreads) void km_ssp_rows_k(const float *__re
 // max(0, base[u][v] + lambda_v - lambda_u) until the first under-full
 // cluster t is settled; the path's rows move one edge each; lambda_v -=
 // min(dist_v, dist_t); the edge rows of the clusters on the path are
-// recomputed.  Sets flags[2] when balanced, flags[3] = augmentations, and
-// clears the counts.
-__global__ __launch_bounds__(kKmSspThreads) void km_ssp_k(const float *__restrict__ S, int n, int k,
-                                                          int m, KmWork W,
+// recomputed.  Sets flags[2] when balanced, flags[3] = augmentations.
+// A chain of latencies: the search runs in one wavefront, its labels in
+// registers, and with LDS (k <= kKmSspLdsK) the edge costs lie in LDS, so a
+// step costs no barrier and no memory round trip.
+constexpr int kKmSspLdsK = 112;
+
+template <bool LDS>
+__global__ __launch_bounds__(kKmSspThreads) void km_ssp_k(int n, int k, int m, KmWork W,
                                                           int32_t *__restrict__ assign) {
+    constexpr int kV = kKmMaxK / 64;  // clusters per lane
     __shared__ double lam[kKmMaxK], dist[kKmMaxK];
-    __shared__ int cnt[kKmMaxK], pred[kKmMaxK], settled[kKmMaxK], chg[kKmMaxK];
-    __shared__ int s_u, s_t, s_excess;
+    __shared__ int cnt[kKmMaxK], pred[kKmMaxK], chg[kKmMaxK];
+    __shared__ int s_t, s_excess;
+    __shared__ SspRowLds R;
+    __shared__ double edges[LDS ? kKmSspLdsK * kKmSspLdsK : 1];
+    double *base = LDS ? edges : W.base;
     int32_t *memb = W.memb;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     for (int j = tid; j < k; j += kKmSspThreads) {
         lam[j] = W.lam[j];
         cnt[j] = W.count[j];
     }
+    if (LDS)
+        for (int i = tid; i < k * k; i += kKmSspThreads) edges[i] = W.base[i];
     __syncthreads();
     int aug = 0;
     for (; aug <= n; ++aug) {
+        for (int v = tid; v < k; v += kKmSspThreads) chg[v] = 0;
         if (wv == 0) {
+            double d[kV], lv[kV];
+            int pr[kV];
+            bool open[kV];
             int ex = 0;
-            for (int j = lane; j < k; j += 64) ex += cnt[j] > m ? cnt[j] - m : 0;
+#pragma unroll
+            for (int q = 0; q < kV; ++q) {
+                const int v = lane + 64 * q, c = v < k ? cnt[v] : m;
+                open[q] = v < k;
+                d[q] = c > m ? 0.0 : INFINITY;
+                lv[q] = v < k ? lam[v] : 0.0;
+                pr[q] = -1;
+                ex += c > m ? c - m : 0;
+            }
 #pragma unroll
             for (int st = 32; st >= 1; st >>= 1) ex += __shfl_xor(ex, st, 64);
-            if (lane == 0) s_excess = ex;
-        }
-        for (int v = tid; v < k; v += kKmSspThreads) {
-            dist[v] = cnt[v] > m ? 0.0 : INFINITY;
-            pred[v] = -1;
-            settled[v] = 0;
-            chg[v] = 0;
+            int t = -1;
+            if (ex > 0) {
+                // Dijkstra until the first under-full cluster is settled
+                for (int step = 0; step < k; ++step) {
+                    double bd = INFINITY;
+                    int bu = 0x7FFFFFFF;
+#pragma unroll
+                    for (int q = 0; q < kV; ++q)
+                        if (open[q] && d[q] < bd) {  // ascending clusters: the first wins ties
+                            bd = d[q];
+                            bu = lane + 64 * q;
+                        }
+                    wave_min(bd, bu, lane);
+                    const int u = __builtin_amdgcn_readfirstlane(bu);
+                    if (u >= k) break;  // nothing within reach
+                    if (cnt[u] < m) {
+                        t = u;
+                        break;
+                    }
+                    const double lu = lam[u];
+#pragma unroll
+                    for (int q = 0; q < kV; ++q) {
+                        const int v = lane + 64 * q;
+                        if (v == u) open[q] = false;
+                        if (open[q]) {
+                            const double nd = bd + fmax(0.0, base[(size_t)u * k + v] + lv[q] - lu);
+                            if (nd < d[q]) {
+                                d[q] = nd;
+                                pr[q] = u;
+                            }
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < kV; ++q) {
+                const int v = lane + 64 * q;
+                if (v < k) {
+                    dist[v] = d[q];
+                    pred[v] = pr[q];
+                }
+            }
+            if (lane == 0) {
+                s_excess = ex;
+                s_t = t;
+            }
         }
         __syncthreads();
         if (s_excess == 0) break;
-        // Dijkstra until the first under-full cluster is settled
-        for (int step = 0; step < k; ++step) {
-            if (wv == 0) {
-                double bd = INFINITY;
-                int bu = 0x7FFFFFFF;
-                for (int v = lane; v < k; v += 64)
-                    if (!settled[v] && (dist[v] < bd || (dist[v] == bd && v < bu))) {
-                        bd = dist[v];
-                        bu = v;
-                    }
-#pragma unroll
-                for (int st = 32; st >= 1; st >>= 1) {
-                    const double od = __shfl_xor(bd, st, 64);
-                    const int ou = __shfl_xor(bu, st, 64);
-                    if (od < bd || (od == bd && ou < bu)) {
-                        bd = od;
-                        bu = ou;
-                    }
-                }
-                if (lane == 0) {
-                    s_u = (bu < k && bd < INFINITY) ? bu : -1;
-                    if (s_u >= 0) settled[s_u] = 1;
-                    s_t = (s_u >= 0 && cnt[s_u] < m) ? s_u : -1;
-                }
-            }
-            __syncthreads();
-            const int u = s_u;
-            if (u < 0 || s_t >= 0) break;
-            for (int v = tid; v < k; v += kKmSspThreads) {
-                if (settled[v]) continue;
-                const double red = fmax(0.0, W.base[(size_t)u * k + v] + lam[v] - lam[u]);
-                const double nd = dist[u] + red;
-                if (nd < dist[v]) {
-                    dist[v] = nd;
-                    pred[v] = u;
-                }
-            }
-            __syncthreads();
-        }
         const int t = s_t;
         if (t < 0) break;  // no path: leaves flags[2] clear
         if (tid == 0) {  // move one row along each edge of the path, t back to its source
@@ -576,18 +747,15 @@ __global__ __launch_bounds__(kKmSspThreads) void km_ssp_k(const float *__restric
                 v = u;
             }
         }
-        __syncthreads();
         const double dt = dist[t];
         for (int v = tid; v < k; v += kKmSspThreads) lam[v] -= fmin(dist[v], dt);
         __syncthreads();
         for (int a = 0; a < k; ++a)
-            if (chg[a]) ssp_row(S, n, k, a, cnt[a], memb, W.base, W.bidx);
+            if (chg[a])
+                ssp_row(W.St, n, k, a, cnt[a], memb, base + (size_t)a * k, W.bidx + (size_t)a * k, R);
         __syncthreads();
     }
-    for (int j = tid; j < k; j += kKmSspThreads) {
-        W.lam[j] = lam[j];
-        W.count[j] = 0;
-    }
+    for (int j = tid; j < k; j += kKmSspThreads) W.lam[j] = lam[j];
     if (tid == 0) {
         W.flags[2] = s_excess == 0 ? 1 : 0;
         W.flags[3] = aug;
@@ -603,6 +771,7 @@ __global__ __launch_bounds__(1024) void km_objective_k(const float *__restrict__
     __shared__ double red[1024];
     const int tid = threadIdx.x;
     double acc = 0.0;
+#pragma unroll 8
     for (int i = tid; i < n; i += 1024) acc += xnorm[i] + (double)S[(size_t)assign[i] * n + i];
     red[tid] = acc;
     __syncthreads();
@@ -615,12 +784,12 @@ __global__ __launch_bounds__(1024) void km_objective_k(const float *__restrict__
 
 // Pi: cluster j's rows, ascending, at perm[j m ..].  One workgroup per
 // cluster, a block scan over the rows in order.
-__global__ __launch_bounds__(256) void km_perm_k(const int32_t *__restrict__ assign, int n, int m,
-                                                 int32_t *__restrict__ perm) {
-    __shared__ int scan[8];
+__global__ __launch_bounds__(1024) void km_perm_k(const int32_t *__restrict__ assign, int n, int m,
+                                                  int32_t *__restrict__ perm) {
+    __shared__ int scan[32];
     const int j = blockIdx.x, tid = threadIdx.x;
     int base = 0;
-    for (int i0 = 0; i0 < n; i0 += 256) {
+    for (int i0 = 0; i0 < n; i0 += 1024) {
         const int i = i0 + tid;
         const int f = (i < n && assign[i] == j) ? 1 : 0;
         int ex, ex1, tot, tot1;
@@ -637,6 +806,7 @@ __global__ __launch_bounds__(256) void km_update_k(const uint16_t *__restrict__ 
     const int j = blockIdx.x, c = blockIdx.y * 256 + threadIdx.x;
     if (c >= D) return;
     double acc = 0.0;
+#pragma unroll 8
     for (int t = 0; t < m; ++t) acc += bf16_to_f32(F[(size_t)perm[(size_t)j * m + t] * D + c]);
     mu[(size_t)j * D + c] = (float)(acc / (double)m);
 }
@@ -649,7 +819,7 @@ template <int NT>
 void launch_dist_nt(const uint16_t *F, int n, int D, int k, const KmWork &W, hipStream_t s) {
     const int blocks = (n + 16 * kKmDistWaves - 1) / (16 * kKmDistWaves);
     hipLaunchKernelGGL(km_dist_k<NT>, dim3(blocks), dim3(64 * kKmDistWaves), 0, s, F, n, D, k,
-                       W.mu3, W.cn, W.S);
+                       W.mu3, W.cn, W.S, W.St);
 }
 
 template <int... Q>
@@ -691,16 +861,16 @@ extern "C" pp_status prunepath_balanced_kmeans(const uint16_t *F, int32_t n, int
     for (int it = 0; it < iters && status == PP_OK; ++it) {
         hipLaunchKernelGGL(km_split_k, dim3(k), dim3(256), 0, s, centroids, k, D, W.mu3, W.cn);
         launch_dist(nt, F, n, D, k, W, s, std::make_integer_sequence<int, kKmMaxK / 16>{});
-        hipLaunchKernelGGL(km_auction_init_k, dim3(1), dim3(256), 0, s, k, W.lam, W.count, W.flags);
+        hipLaunchKernelGGL(km_auction_init_k, dim3(1), dim3(256), 0, s, k, W.lam, W.flags);
         int r = 0, used = 0;
         bool done = false;
         while (!done && r < kKmAuctionRounds) {
             const int r1 = r + kKmBatch;
             for (; r < r1; ++r) {
-                hipLaunchKernelGGL(km_bid_k, dim3(nbid), dim3(kKmBidThreads), 0, s, W.S, n, k, r,
-                                   W, assign);
-                hipLaunchKernelGGL(km_price_k, dim3(k), dim3(kKmPriceThreads), 0, s, n, k, m, r,
-                                   nbid, W);
+                hipLaunchKernelGGL(km_bid_k, dim3(nbid), dim3(64 * kKmBidWaves), 0, s, W.S, n, k,
+                                   r, W, assign);
+                hipLaunchKernelGGL(km_price_k, dim3(k), dim3(kKmPriceThreads), 0, s, n, m, r, nbid,
+                                   std::max(kKmEps0 * std::pow(0.9, r), 0x1p-22), W, assign);
             }
             int32_t fl[4];
             if (hipMemcpyAsync(fl, W.flags, sizeof fl, hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -712,13 +882,18 @@ extern "C" pp_status prunepath_balanced_kmeans(const uint16_t *F, int32_t n, int
             used = fl[2] != 0 ? fl[3] : r;
         }
         if (!done) {  // route the remaining excess by shortest paths
-            // one more bid round: the argmax, counts and member lists of the
-            // current prices (no price round follows it)
-            hipLaunchKernelGGL(km_bid_k, dim3(nbid), dim3(kKmBidThreads), 0, s, W.S, n, k, r, W,
+            // one more bid round: the argmax of the current prices (no price
+            // round follows it), and the clusters' member lists
+            hipLaunchKernelGGL(km_bid_k, dim3(nbid), dim3(64 * kKmBidWaves), 0, s, W.S, n, k, r, W,
                                assign);
-            hipLaunchKernelGGL(km_ssp_rows_k, dim3(k), dim3(kKmSspThreads), 0, s, W.S, n, k, W);
-            hipLaunchKernelGGL(km_ssp_k, dim3(1), dim3(kKmSspThreads), 0, s, W.S, n, k, m, W,
-                               assign);
+            hipLaunchKernelGGL(km_members_k, dim3(k), dim3(1024), 0, s, assign, n, W);
+            hipLaunchKernelGGL(km_ssp_rows_k, dim3(k), dim3(kKmSspThreads), 0, s, n, k, W);
+            if (k <= kKmSspLdsK)
+                hipLaunchKernelGGL(km_ssp_k<true>, dim3(1), dim3(kKmSspThreads), 0, s, n, k, m, W,
+                                   assign);
+            else
+                hipLaunchKernelGGL(km_ssp_k<false>, dim3(1), dim3(kKmSspThreads), 0, s, n, k, m,
+                                   W, assign);
             int32_t fl[4];
             if (hipMemcpyAsync(fl, W.flags, sizeof fl, hipMemcpyDeviceToHost, s) != hipSuccess ||
                 hipStreamSynchronize(s) != hipSuccess)
@@ -734,7 +909,7 @@ extern "C" pp_status prunepath_balanced_kmeans(const uint16_t *F, int32_t n, int
         if (objective)
             hipLaunchKernelGGL(km_objective_k, dim3(1), dim3(1024), 0, s, W.S, W.xnorm, assign, n,
                                objective + it);
-        hipLaunchKernelGGL(km_perm_k, dim3(k), dim3(256), 0, s, assign, n, m, perm);
+        hipLaunchKernelGGL(km_perm_k, dim3(k), dim3(1024), 0, s, assign, n, m, perm);
         hipLaunchKernelGGL(km_update_k, dim3(k, (D + 255) / 256), dim3(256), 0, s, F, D, m, perm,
                            centroids);
     }

@@ -1,0 +1,49 @@
+"""Balanced k-means where its auction and distance kernels change path: more
+rows than a price workgroup gathers at once, one cluster holding more rows
+than fit its LDS list, cluster counts that do not divide over the bid
+wavefronts or fill a distance tile, and the largest number of tiles.  Checked
+by the duality certificate (test_gpu_kmeans.py), exact balance and Pi."""
+import numpy as np
+import pytest
+
+import paper_2605_28283_amd as pp
+from paper_2605_28283_amd.workloads import bf16_to_f32, make_clustered_features
+from test_gpu_kmeans import check_certificate, check_perm, run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    pp.load()
+    torch.cuda.init()
+
+
+# (130, 13): less than one bid workgroup's rows twice over, k = 13;
+# (17408, 17): a second batch of rows in the price kernel; (1250, 250): two
+# batches of clusters per bid wavefront, 16 distance tiles
+@pytest.mark.parametrize("n,D,k", [(130, 64, 13), (17408, 64, 17), (1250, 128, 250)])
+def test_kmeans_round_edges(n, D, k):
+    F, _, init_rows = make_clustered_features(n, D, k, 31 + k)
+    X = bf16_to_f32(F).astype(np.float64)
+    r = run(F, k, X[init_rows], 1)
+    check_perm(r, k)
+    check_certificate(X, X[init_rows], r["assign"], r["prices"])
+
+
+def test_kmeans_list_longer_than_lds():
+    """20480 rows, of which all but a few first choose cluster 0 (the other
+    centroids lie outside the cloud): its list is read from memory."""
+    n, D, k = 20480, 64, 4
+    F, _, init_rows = make_clustered_features(n, D, k, 41)
+    X = bf16_to_f32(F).astype(np.float64)
+    init = np.tile(X.mean(0), (k, 1)).astype(np.float32)
+    init[1:] += 0.1 * np.eye(k - 1, D, dtype=np.float32)
+    s = (init.astype(np.float64) ** 2).sum(1) - 2.0 * X @ init.T.astype(np.float64)
+    assert (s.argmin(1) == 0).sum() > 8192
+    r = run(F, k, init, 1)
+    check_perm(r, k)
+    check_certificate(X, init, r["assign"], r["prices"])
