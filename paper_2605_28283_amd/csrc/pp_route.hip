@@ -37,11 +37,15 @@ constexpr int kLgTiles = 4;       // 16-token tiles per logits workgroup
 
 
 __global__ __launch_bounds__(1024) void logits_k(RouteParams P) {
-    __shared__ uint4 xs[kLgTiles][kRouteWaves][64];  // [token tile][K-step][lane]: A fragments
+    // the slice's token rows: [token tile][K-step pair][8 rows][row, 16-byte
+    // chunk], chunk c of row r at place c ^ (r % 8), so that both the stores
+    // and a fragment's reads (row lane % 16, chunk 4 (s % 2) + lane / 16)
+    // spread over all banks
+    __shared__ uint4 xs[kLgTiles][kRouteWaves / 2][2][64];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int tb = blockIdx.x / P.KSr, ks = blockIdx.x - tb * P.KSr;
     if (P.build_plan && blockIdx.x == 0 && tid < P.E) P.emask[tid] = 0ull;
-    const int s_end = min(kRouteWaves, P.NS - ks * kRouteWaves);  // K-steps in this slice
+    const int s_end = min(kRouteWaves, P.NS - ks * kRouteWaves);  // K-steps in this slice (even)
     // wavefront wv < nEt: the router fragments of expert tile wv for the
     // slice, loaded first so that their round trip overlaps the token staging
     // (native vectors: an array of uint4 would not stay in registers; an
@@ -61,25 +65,32 @@ __global__ __launch_bounds__(1024) void logits_k(RouteParams P) {
             for (int s = 0; s < kRouteWaves; ++s) b[s] = wr[min(s, s_end - 1) * (kKStep / 8)];
         }
     }
-    // stage the block's token rows of this slice as MFMA A fragments; every
-    // load is issued (addresses clamped into the operands), then rows past T
-    // and K-steps past the slice are zeroed
+    // stage the block's token rows of this slice; every load is issued
+    // (addresses clamped into the operands), then rows past T and K-steps past
+    // the slice are zeroed.  A wavefront takes the 128 bytes that a pair of
+    // K-steps reads of eight rows of every tile, whole cache lines (64 bytes
+    // of sixteen rows fetched each line twice).
     {
-        const int s = wv, sc = min(s, s_end - 1);  // thread (wv, lane) stages K-step wv of every tile
+        const int p = wv >> 1, hf = wv & 1, r8 = 8 * hf + (lane >> 3);
+        const int col = (ks * kRouteWaves + min(2 * p, s_end - 2)) * kKStep +
+                        8 * ((lane & 7) ^ (lane >> 3));
         u32x4_t v[kLgTiles];  // native vectors: the selects below stay in registers
 #pragma unroll
         for (int j = 0; j < kLgTiles; ++j) {
-            const int t = min(tb * 16 * kLgTiles + 16 * j + (lane & 15), P.T - 1);
-            v[j] = *reinterpret_cast<const u32x4_t *>(P.x + (size_t)t * P.d +
-                                                      (ks * kRouteWaves + sc) * kKStep + 8 * (lane >> 4));
+            const int t = min(tb * 16 * kLgTiles + 16 * j + r8, P.T - 1);
+            v[j] = *reinterpret_cast<const u32x4_t *>(P.x + (size_t)t * P.d + col);
         }
 #pragma unroll
         for (int j = 0; j < kLgTiles; ++j) {
-            const int t = tb * 16 * kLgTiles + 16 * j + (lane & 15);
-            const u32x4_t w = (t < P.T && s < s_end) ? v[j] : u32x4_t{0u, 0u, 0u, 0u};
-            xs[j][s][lane] = make_uint4(w.x, w.y, w.z, w.w);
+            const int t = tb * 16 * kLgTiles + 16 * j + r8;
+            const u32x4_t w = (t < P.T && 2 * p < s_end) ? v[j] : u32x4_t{0u, 0u, 0u, 0u};
+            xs[j][p][hf][lane] = make_uint4(w.x, w.y, w.z, w.w);
         }
     }
+    const int r = lane & 7, rh = (lane >> 3) & 1;
+    auto frag = [&](int j, int s) {
+        return xs[j][s >> 1][rh][8 * r + ((4 * (s & 1) + (lane >> 4)) ^ r)];
+    };
     __syncthreads();
     // wavefront wv: expert tile wv for every token tile, K-steps of the slice
     // accumulated in order in the MFMA accumulators
@@ -96,8 +107,8 @@ __global__ __launch_bounds__(1024) void logits_k(RouteParams P) {
                 for (int s = 0; s < kRouteWaves; ++s) {
                     if (s < s_end) {
                         const uint4 bs = make_uint4(b[s].x, b[s].y, b[s].z, b[s].w);
-                        acc[j0] = mfma16(xs[j0][s][lane], bs, acc[j0]);
-                        if (j0 + 1 < ntile) acc[j0 + 1] = mfma16(xs[j0 + 1][s][lane], bs, acc[j0 + 1]);
+                        acc[j0] = mfma16(frag(j0, s), bs, acc[j0]);
+                        if (j0 + 1 < ntile) acc[j0 + 1] = mfma16(frag(j0 + 1, s), bs, acc[j0 + 1]);
                     }
                 }
             }
@@ -107,7 +118,7 @@ __global__ __launch_bounds__(1024) void logits_k(RouteParams P) {
     // slice: staged in LDS (lane holds tokens 4 (lane / 16) + i of each tile,
     // expert ec), then written out with whole-row stores
     __syncthreads();
-    float *ob = reinterpret_cast<float *>(&xs[0][0][0]);
+    float *ob = reinterpret_cast<float *>(&xs[0][0][0][0]);
     static_assert(sizeof(xs) >= 16 * kLgTiles * kMaxExperts * sizeof(float), "staging fits");
     if (wv < P.nEt && ve) {
 #pragma unroll
