@@ -435,8 +435,9 @@ __global__ __launch_bounds__(256) void dispatch_k(const uint32_t *__restrict__ s
 // is a fifth shorter).  A block of 64 rows by 512 tokens, staged in LDS and
 // multiplied by whichever wavefronts the run's tiles fill, with two barriers
 // per expert, took (LLaMA-3-8B shape) 132 us for 2048 tokens at tau 0.7 and
-// 1550 us for 16384 at tau 0.9; this takes 98 and 1110.  For 777 tokens of a
-// 1024-wide GELU layer (16-row blocks before): 51 and 23.
+// 1550 us for 16384 at tau 0.9; this takes 95 and 1080 (98 and 1150 with h
+// carried as 64-byte pieces of sixteen rows).  For 777 tokens of a 1024-wide
+// GELU layer (16-row blocks before): 51 and 23.
 constexpr int kTileAhead = 8;      // tiles in flight per carrying wavefront
 constexpr int kWAhead = 2;         // experts whose down rows are loaded ahead
 constexpr int kRowThreads = 512;
@@ -450,7 +451,8 @@ static_assert(kTileAhead % 2 == 0, "tile k lies in slot k % 2");
 __device__ __forceinline__ int row_off(int t) { return t * (kRowBlock * 4); }
 
 struct DownRowsLds {
-    uint4 h[2][2][4][64];      // [slot][hi, lo][K-step][lane]: A fragments
+    uint4 h[2][2][16][16];     // [slot][hi, lo][place]: the token's h, 16-byte piece c of
+                               // place q at c ^ q (spreads a fragment's reads over all banks)
     int off[2][16];            // [slot][place]: the token's row_off
     uint16_t ent[kMaxExperts]; // experts with tokens in the chunk, ascending: e | tiles << 8
     int scan[2 * (kRowThreads / 64)];
@@ -467,11 +469,18 @@ struct RowTile {
     int4 off;  // the lane's four tokens (places 4 (lane / 16) + i)
 };
 
+// The lane's 16 bytes of K-step s of a slot's hi or lo: place lane % 16, piece
+// 4 s + lane / 16.
+__device__ __forceinline__ uint4 rows_frag(const uint4 (&h)[16][16], int s, int lane) {
+    const int q = lane & 15;
+    return h[q][(4 * s + (lane >> 4)) ^ q];
+}
+
 __device__ __forceinline__ void rows_read(RowTile &t, const DownRowsLds &S, int slot, int lane) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-        t.hi[s] = S.h[slot][0][s][lane];
-        t.lo[s] = S.h[slot][1][s][lane];
+        t.hi[s] = rows_frag(S.h[slot][0], s, lane);
+        t.lo[s] = rows_frag(S.h[slot][1], s, lane);
     }
     t.off = *reinterpret_cast<const int4 *>(&S.off[slot][4 * (lane >> 4)]);
 }
@@ -515,8 +524,8 @@ __device__ __forceinline__ void rows_step(const DownRowsLds &S, char *yb, const 
         // not waited for.
         if (j == 5) asm volatile("s_waitcnt lgkmcnt(6)\n\ts_barrier" ::: "memory");
         if (j >= 6 && j < 10) {
-            nxt.hi[j - 6] = S.h[slot][0][j - 6][lane];
-            nxt.lo[j - 6] = S.h[slot][1][j - 6][lane];
+            nxt.hi[j - 6] = rows_frag(S.h[slot][0], j - 6, lane);
+            nxt.lo[j - 6] = rows_frag(S.h[slot][1], j - 6, lane);
         }
         if (j == 10) nxt.off = *reinterpret_cast<const int4 *>(&S.off[slot][4 * (lane >> 4)]);
         if (LOAD && (j & 1)) Wn[j >> 1] = ldg16(wn + (j >> 1) * 512);
@@ -550,26 +559,28 @@ __device__ __forceinline__ void rows_expert(const DownRowsLds &S, char *yb, RowT
 }
 
 // A tile on its way through a carrying wavefront's registers.  The wavefront
-// carries hi or lo (src) in two of the four K-steps, 128 consecutive bytes of
-// each row; places past the run repeat its last row.
+// carries hi or lo (src) of eight places, two loads of four whole rows each
+// (1 KiB in a piece where the run fills them); places past the run repeat its
+// last row.
 struct Carry {
     u32x4_t v[2];
     int tok, last;  // last: the tile's last place with a token
 };
 
-// d: the tile's list word; col: byte offset of the lane's first 16 bytes in
-// its row
+// d: the tile's list word; q0: the wavefront's first place
 __device__ __forceinline__ void carry_issue(Carry &c, unsigned d, const uint16_t *src,
-                                            const int32_t *pair_tok, unsigned col, int lane) {
+                                            const int32_t *pair_tok, int q0, int lane) {
     c.last = (int)(d >> 24);
     const size_t r0 = d & 0xFFFFFFu;
-    const unsigned q = (unsigned)min(lane & 15, c.last);
     const char *row = reinterpret_cast<const char *>(src + r0 * kExpertWidth);
-    const unsigned o = q * (kExpertWidth * 2u) + col;
-    c.v[0] = *reinterpret_cast<const u32x4_t *>(row + o);
-    c.v[1] = *reinterpret_cast<const u32x4_t *>(row + o + kKStep * 2);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const unsigned q = (unsigned)min(q0 + 4 * i + (lane >> 4), c.last);
+        c.v[i] = *reinterpret_cast<const u32x4_t *>(row + (q * (kExpertWidth * 2u) +
+                                                           16u * (lane & 15)));
+    }
     c.tok = *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(pair_tok + r0) +
-                                               4u * q);
+                                               4u * (unsigned)min(lane & 15, c.last));
 }
 
 // A unit's place: the row blocks in groups of kRowGroup, a group's token
@@ -634,15 +645,14 @@ __device__ __forceinline__ void rows_multiply(const DownRowsLds &S, char *yb, co
 // with one wait each: past the last tile it carries that tile again.
 __device__ __forceinline__ void rows_carry(DownRowsLds &S, const uint32_t *list, const DNParams &P,
                                            int C, int t0, int steps, int p, int lane) {
-    const int part = p & 1, s0 = 2 * (p >> 1);
+    const int part = p & 1, q0 = 8 * (p >> 1);
     const uint16_t *src = part ? P.h_lo : P.h_hi;
-    const unsigned col = (unsigned)(s0 * kKStep + 8 * (lane >> 4)) * 2u;
     auto word = [&](int k) { return (int)list[min(k, steps - 1)]; };
     Carry ring[kTileAhead];
 #pragma unroll
     for (int i = 0; i < kTileAhead; ++i) {
         carry_issue(ring[i], (unsigned)__builtin_amdgcn_readfirstlane(word(i)), src, P.pair_tok,
-                    col, lane);
+                    q0, lane);
         __builtin_amdgcn_sched_barrier(0);  // issued in order: the loop's waits count on it
     }
     int next = word(kTileAhead);
@@ -654,13 +664,16 @@ __device__ __forceinline__ void rows_carry(DownRowsLds &S, const uint32_t *list,
             // nothing of a later tile is computed here: it would be waited for
             __builtin_amdgcn_sched_barrier(0);
             asm volatile("" : "+v"(cr.tok));
-            *reinterpret_cast<u32x4_t *>(&S.h[i % 2][part][s0][lane]) = cr.v[0];
-            *reinterpret_cast<u32x4_t *>(&S.h[i % 2][part][s0 + 1][lane]) = cr.v[1];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int q = q0 + 4 * u + (lane >> 4);
+                *reinterpret_cast<u32x4_t *>(&S.h[i % 2][part][q][(lane & 15) ^ q]) = cr.v[u];
+            }
             // (every 16 lanes of the four wavefronts store the same offsets)
             const int q = lane & 15;
             S.off[i % 2][q] = row_off(q <= cr.last ? cr.tok - t0 : C);
             next = word(k0 + i + kTileAhead + 1);
-            carry_issue(ring[i], d, src, P.pair_tok, col, lane);
+            carry_issue(ring[i], d, src, P.pair_tok, q0, lane);
             __syncthreads();  // tile k0 + i is in its slot; the one before has been read
         }
     }
