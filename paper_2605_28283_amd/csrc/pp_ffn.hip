@@ -519,9 +519,8 @@ __device__ __forceinline__ void rows_step(const DownRowsLds &S, char *yb, const 
         a[j & 1] = mfma16((j & 2) ? cur.lo[s] : cur.hi[s], W[4 * (j & 1) + s], a[j & 1]);
         if (j < 4) y[j] = sums_load(yb, prev, j);
         // Tile k + 1 is in its slot, and this wavefront has read all of tile k:
-        // LDS accesses end in order, and the only ones issued since are the
-        // eight of y (7 still in flight would leave one to spare).  They are
-        // not waited for.
+        // LDS accesses end in order, and eight of y were issued after those
+        // reads (tile 0's were waited for), of which six may be in flight.
         if (j == 5) asm volatile("s_waitcnt lgkmcnt(6)\n\ts_barrier" ::: "memory");
         if (j >= 6 && j < 10) {
             nxt.hi[j - 6] = rows_frag(S.h[slot][0], j - 6, lane);
@@ -618,6 +617,8 @@ __device__ __forceinline__ void rows_multiply(const DownRowsLds &S, char *yb, co
     __syncthreads();  // tile 0 is in its slot
     RowTile A, B;
     rows_read(A, S, 0, lane);
+    // the first step has no sums to store between these reads and its barrier
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     RowSums prev;
     prev.a0 = prev.a1 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
