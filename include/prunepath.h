@@ -256,9 +256,9 @@ pp_status prunepath_router_loss_noalloc(const float *g, int32_t B, int32_t E, fl
  * Limits: 1 <= k <= 256, k <= n <= 65536, n % k == 0, 64 <= D <= 16384,
  * D % 64 == 0 (PP_EINVAL otherwise; the workspace query returns 0).  The
  * call blocks: it synchronises hip_stream to follow the auction.
- * PP_ENOTCONVERGED when an assignment needs more than 32768 auction rounds
- * (possible when rows are exact duplicates of each other); outputs then hold
- * the last unbalanced state. */
+ * PP_ENOTCONVERGED when an assignment cannot be balanced, which takes features
+ * or centroids that are not finite, or that overflow fp32 in ||mu||^2 - 2 F.mu;
+ * outputs then hold the last unbalanced state, every assign[i] in 0 .. k - 1. */
 size_t prunepath_kmeans_workspace(int32_t n, int32_t D, int32_t k); /* 0 for bad sizes */
 pp_status prunepath_balanced_kmeans(const uint16_t *F, int32_t n, int32_t D, int32_t k,
                                     const float *init_centroids, int32_t iters, int32_t *assign,

@@ -352,7 +352,8 @@ __global__ __launch_bounds__(64 * kKmBidWaves) void km_bid_k(const float *__rest
         W.margin[i] = isinf(mg) ? 3.0e38f : __double2float_ru(mg);
     }
     if (r == 0) {  // eps scale: sum of per-row spreads, fixed order
-        double sp = valid ? (double)v.smax - (double)v.smin : 0.0;
+        // (a row of NaNs has none)
+        double sp = valid && v.smin <= v.smax ? (double)v.smax - (double)v.smin : 0.0;
 #pragma unroll
         for (int st = 32; st >= 1; st >>= 1) sp += __shfl_xor(sp, st, 64);
         if (lane == 0) W.part[blockIdx.x] = sp;
@@ -637,6 +638,10 @@ __device__ __forceinline__ void wave_min(double &d, int &v, int lane) {
 // cluster t is settled; the path's rows move one edge each; lambda_v -=
 // min(dist_v, dist_t); the edge rows of the clusters on the path are
 // recomputed.  Sets flags[2] when balanced, flags[3] = augmentations.
+// An edge without a row (base = +inf: u is empty, or its rows' values at v are
+// not numbers) is never taken, whatever the prices make of its cost, as
+// bidx[u][v] then names no row; prices that are not finite (features or
+// centroids were not) end the step unbalanced, for they order nothing.
 // A chain of latencies: the search runs in one wavefront, its labels in
 // registers, and with LDS (k <= kKmSspLdsK) the edge costs lie in LDS, so a
 // step costs no barrier and no memory round trip.
@@ -669,6 +674,7 @@ __global__ __launch_bounds__(kKmSspThreads) void km_ssp_k(int n, int k, int m, K
             int pr[kV];
             bool open[kV];
             int ex = 0;
+            bool finite = true;
 #pragma unroll
             for (int q = 0; q < kV; ++q) {
                 const int v = lane + 64 * q, c = v < k ? cnt[v] : m;
@@ -676,12 +682,13 @@ __global__ __launch_bounds__(kKmSspThreads) void km_ssp_k(int n, int k, int m, K
                 d[q] = c > m ? 0.0 : INFINITY;
                 lv[q] = v < k ? lam[v] : 0.0;
                 pr[q] = -1;
+                finite = finite && isfinite(lv[q]);
                 ex += c > m ? c - m : 0;
             }
 #pragma unroll
             for (int st = 32; st >= 1; st >>= 1) ex += __shfl_xor(ex, st, 64);
             int t = -1;
-            if (ex > 0) {
+            if (ex > 0 && __all(finite)) {
                 // Dijkstra until the first under-full cluster is settled
                 for (int step = 0; step < k; ++step) {
                     double bd = INFINITY;
@@ -705,8 +712,9 @@ __global__ __launch_bounds__(kKmSspThreads) void km_ssp_k(int n, int k, int m, K
                         const int v = lane + 64 * q;
                         if (v == u) open[q] = false;
                         if (open[q]) {
-                            const double nd = bd + fmax(0.0, base[(size_t)u * k + v] + lv[q] - lu);
-                            if (nd < d[q]) {
+                            const double c = base[(size_t)u * k + v];
+                            const double nd = bd + fmax(0.0, c + lv[q] - lu);
+                            if (c < INFINITY && nd < d[q]) {
                                 d[q] = nd;
                                 pr[q] = u;
                             }

@@ -47,3 +47,47 @@ def test_kmeans_list_longer_than_lds():
     r = run(F, k, init, 1)
     check_perm(r, k)
     check_certificate(X, init, r["assign"], r["prices"])
+
+
+@pytest.mark.parametrize("what,iters,ok", [
+    ("rows", 1, True), ("rows", 2, False), ("many rows", 1, False), ("row inf", 1, True),
+    ("centroid", 1, False), ("centroid overflow", 1, False)])
+def test_kmeans_values_that_are_not_finite(what, iters, ok):
+    """Three rows of NaNs, or one of infinities (times the zero low parts of a
+    bf16 centroid: NaNs again), still go somewhere; more of them than a cluster
+    takes, a NaN centroid (the three rows' own one in the second iteration) or
+    one whose norm overflows fp32 leave nothing to balance by: the call says so,
+    with every row in some cluster, and the next call gives what it gave
+    before."""
+    import torch
+    n, D, k = 256, 64, 8
+    F, _, init_rows = make_clustered_features(n, D, k, 51)
+    init = bf16_to_f32(F)[init_rows].copy()
+    good = run(F, k, init, 1)
+    bad = F.copy()
+    free = np.setdiff1d(np.arange(n), init_rows)
+    if what.endswith("rows"):
+        bad[free[:40 if what == "many rows" else 3]] = 0x7FC0
+    elif what == "row inf":
+        bad[free[0], :2] = (0x7F80, 0xFF80)
+    else:
+        init[3] = float("nan") if what == "centroid" else 1e25
+    if ok:
+        check_perm(run(bad, k, init, iters), k)
+    else:
+        Fd = torch.from_numpy(bad.view(np.int16)).cuda()
+        mu = torch.from_numpy(np.ascontiguousarray(init, np.float32)).cuda()
+        ws = torch.empty(pp.prunepath_kmeans_workspace(n, D, k), dtype=torch.uint8, device="cuda")
+        assign = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        perm = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        print("kmeans not finite: %s, iters=%d" % (what, iters), flush=True)
+        with pytest.raises(pp.PrunePathError) as err:
+            pp.prunepath_balanced_kmeans(Fd, n, D, k, mu, iters, assign, perm, torch.empty_like(mu),
+                                         ws)
+        assert err.value.status == pp.PP_ENOTCONVERGED
+        torch.cuda.synchronize()
+        a = assign.cpu().numpy()
+        assert a.min() >= 0 and a.max() < k
+    again = run(F, k, bf16_to_f32(F)[init_rows], 1)
+    for key in ("assign", "perm", "centroids", "prices"):
+        np.testing.assert_array_equal(good[key], again[key])
