@@ -15,7 +15,7 @@
 //               When no cluster is over-full all hold exactly m rows, and an
 //               argmax assignment that is balanced is optimal by LP duality,
 //               whatever eps was; eps only ends price wars, so it decays
-//               geometrically (0.05 scale * 0.9^r, floor 2^-22 scale).  Small
+//               geometrically (0.3 scale * 0.9^r, floor 2^-22 scale).  Small
 //               steps cannot move a price far, so after kKmAuctionRounds
 //               rounds the rest of the excess is routed by successive
 //               shortest paths on the k-node cluster graph (edge a -> b: the
@@ -52,10 +52,14 @@ constexpr int kKmBidRows = 64;         // rows per bid workgroup, one per lane
 constexpr int kKmBidWaves = 8;         // its wavefronts, each an eighth of the clusters
 constexpr int kKmPriceThreads = 1024;
 constexpr int kKmAuctionRounds = 128;  // price rounds before the shortest-path finish
-// eps of round 0, in units of the rows' mean spread of s.  From 0.3 on the
-// first 17 rounds only overshoot: 0.05 reaches the same excess that many
-// rounds earlier (14336 x 112, planted groups), 0.01 leaves price wars behind.
-constexpr double kKmEps0 = 0.05;
+// eps of round 0, in units of the rows' mean spread of s.  The steps of all
+// rounds together (ten times eps0) are about as far as a price moves, and rows
+// of unequal norm need prices far apart: from 0.05 on, rows scaled by
+// LogNormal(0, 0.2) leave 108 to 376 of the excess to the shortest-path finish
+// (0.04 - 0.2 ms a unit), 0.3 leaves 3 to 11 (8192 x 64 and 14336 x 112,
+// planted groups or none).  On rows of one norm 0.05 ends up to 20 rounds (0.2
+// ms) earlier.  Steps that follow the excess instead end in price wars.
+constexpr double kKmEps0 = 0.3;
 constexpr int kKmBatch = 64;           // rounds enqueued between convergence checks
 constexpr int kKmSspThreads = 1024;
 

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import paper_2605_28283_amd as pp
-from paper_2605_28283_amd.workloads import bf16_to_f32, make_clustered_features
+from paper_2605_28283_amd.workloads import bf16_bits, bf16_to_f32, make_clustered_features
 from test_gpu_kmeans import check_certificate, check_perm, run
 
 pytestmark = pytest.mark.gpu
@@ -91,3 +91,20 @@ def test_kmeans_values_that_are_not_finite(what, iters, ok):
     again = run(F, k, bf16_to_f32(F)[init_rows], 1)
     for key in ("assign", "perm", "centroids", "prices"):
         np.testing.assert_array_equal(good[key], again[key])
+
+
+@pytest.mark.parametrize("n,D,k,centre_std,sigma", [
+    (8192, 256, 64, 0.02, 0.2), (8192, 256, 64, 0.0, 0.2), (4096, 256, 32, 0.02, 0.3)])
+def test_kmeans_rows_of_unequal_norm(n, D, k, centre_std, sigma):
+    """Rows scaled by LogNormal(0, sigma), planted groups or none: the price
+    rounds alone bring the excess down to a few rows (at most 8 in a simulation
+    in fp64), as the shortest-path finish moves one row at a time.  Steps a
+    sixth as large leave it 107 rows or more."""
+    F, _, init_rows = make_clustered_features(n, D, k, 61, centre_std=centre_std)
+    scale = np.random.default_rng(62).lognormal(0.0, sigma, (n, 1)).astype(np.float32)
+    F = bf16_bits(bf16_to_f32(F) * scale)
+    X = bf16_to_f32(F).astype(np.float64)
+    r = run(F, k, X[init_rows], 1)
+    assert r["rounds"][0] <= 128 + 32
+    check_perm(r, k)
+    check_certificate(X, X[init_rows], r["assign"], r["prices"])
