@@ -539,7 +539,8 @@ __device__ __forceinline__ void ssp_row(const float *__restrict__ St, int n, int
                                         const int32_t *memb, double *base, int32_t *bidx,
                                         SspRowLds &R) {
     constexpr int kWaves = kKmSspThreads / 64, kV = kKmMaxK / 64, kB = 8;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     double best[kV];
     int bi[kV];
 #pragma unroll
@@ -553,25 +554,30 @@ __device__ __forceinline__ void ssp_row(const float *__restrict__ St, int n, int
         __syncthreads();
         for (int u0 = wv; u0 < nt; u0 += kB * kWaves) {
             int row[kB];
-            float own[kB], sv[kB][kV];
+            float sv[kB][kV];
 #pragma unroll
             for (int u = 0; u < kB; ++u) {
-                row[u] = R.row[min(u0 + u * kWaves, nt - 1)];  // past the batch: its last row again
+                // past the batch: its last row again
+                row[u] = __builtin_amdgcn_readfirstlane(R.row[min(u0 + u * kWaves, nt - 1)]);
                 const float *p = St + (size_t)row[u] * k;
-                own[u] = p[a];
 #pragma unroll
                 for (int q = 0; q < kV; ++q) sv[u][q] = 64 * q < k ? p[min(lane + 64 * q, k - 1)] : 0.f;
             }
 #pragma unroll
-            for (int u = 0; u < kB; ++u)
+            for (int u = 0; u < kB; ++u) {
+                float own = sv[u][0];
+#pragma unroll
+                for (int q = 1; q < kV; ++q) own = a >> 6 == q ? sv[u][q] : own;
+                own = lane_value(own, a & 63);
 #pragma unroll
                 for (int q = 0; q < kV; ++q) {
-                    const double v = (double)sv[u][q] - (double)own[u];
+                    const double v = (double)sv[u][q] - (double)own;
                     if (v < best[q] || (v == best[q] && row[u] < bi[q])) {
                         best[q] = v;
                         bi[q] = row[u];
                     }
                 }
+            }
         }
         __syncthreads();
     }
