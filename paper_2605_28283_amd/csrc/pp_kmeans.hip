@@ -653,9 +653,15 @@ __device__ __forceinline__ void wave_min(double &d, int &v, int lane) {
 // bidx[u][v] then names no row; prices that are not finite (features or
 // centroids were not) end the step unbalanced, for they order nothing.
 // A chain of latencies: the search runs in one wavefront, its labels in
-// registers, and with LDS (k <= kKmSspLdsK) the edge costs lie in LDS, so a
-// step costs no barrier and no memory round trip.
-constexpr int kKmSspLdsK = 112;
+// registers, and with LDS the edge costs lie in LDS, so a step costs no barrier
+// and no memory round trip: whenever the k x k of them fit beside the rest
+// (k <= 126: 127 units of excess among 126 clusters of 128 rows of 512, a whole
+// call: 19.3 ms, 21.7 ms with the costs in memory).  16: the two ints behind the
+// arrays, and padding.
+constexpr int kKmSspFixed = 2 * kKmMaxK * sizeof(double) + 3 * kKmMaxK * sizeof(int) +
+                            sizeof(SspRowLds) + 16;
+constexpr int kKmSspEdges = (160 * 1024 - kKmSspFixed) / 16 * 2;
+static_assert(kKmSspEdges >= 126 * 126, "edge costs of 126 clusters");
 
 template <bool LDS>
 __global__ __launch_bounds__(kKmSspThreads) void km_ssp_k(int n, int k, int m, KmWork W,
@@ -665,7 +671,7 @@ __global__ __launch_bounds__(kKmSspThreads) void km_ssp_k(int n, int k, int m, K
     __shared__ int cnt[kKmMaxK], pred[kKmMaxK], chg[kKmMaxK];
     __shared__ int s_t, s_excess;
     __shared__ SspRowLds R;
-    __shared__ double edges[LDS ? kKmSspLdsK * kKmSspLdsK : 1];
+    __shared__ double edges[LDS ? kKmSspEdges : 1];
     double *base = LDS ? edges : W.base;
     int32_t *memb = W.memb;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -906,7 +912,7 @@ extern "C" pp_status prunepath_balanced_kmeans(const uint16_t *F, int32_t n, int
                                assign);
             hipLaunchKernelGGL(km_members_k, dim3(k), dim3(1024), 0, s, assign, n, W);
             hipLaunchKernelGGL(km_ssp_rows_k, dim3(k), dim3(kKmSspThreads), 0, s, n, k, W);
-            if (k <= kKmSspLdsK)
+            if (k * k <= kKmSspEdges)
                 hipLaunchKernelGGL(km_ssp_k<true>, dim3(1), dim3(kKmSspThreads), 0, s, n, k, m, W,
                                    assign);
             else

@@ -8,7 +8,7 @@ import pytest
 
 import paper_2605_28283_amd as pp
 from paper_2605_28283_amd.workloads import bf16_bits, bf16_to_f32, make_clustered_features
-from test_gpu_kmeans import check_certificate, check_perm, run
+from test_gpu_kmeans import check_certificate, check_perm, run, step_parity
 
 pytestmark = pytest.mark.gpu
 
@@ -108,3 +108,22 @@ def test_kmeans_rows_of_unequal_norm(n, D, k, centre_std, sigma):
     assert r["rounds"][0] <= 128 + 32
     check_perm(r, k)
     check_certificate(X, X[init_rows], r["assign"], r["prices"])
+
+
+# edge costs in LDS up to 126 clusters, in memory from 127 on; 160, 250, 256:
+# the second half of an edge row's minima
+@pytest.mark.parametrize("n,D,k", [(1008, 64, 126), (1016, 64, 127), (960, 64, 160),
+                                   (1250, 128, 250), (768, 64, 256)])
+def test_kmeans_finish_with_many_clusters(n, D, k):
+    """Well-separated groups of which some hold several initial rows: the price
+    rounds leave 17 rows or more (simulated in fp64) to the shortest-path
+    finish, whose result is the exact optimum."""
+    from oracle import kmeans
+    F, group, init_rows = make_clustered_features(n, D, k, 12, centre_std=0.05, noise_std=0.005)
+    X = bf16_to_f32(F).astype(np.float64)
+    init = X[init_rows]
+    r = run(F, k, init, 1)
+    assert r["rounds"][0] > 128
+    check_perm(r, k)
+    step_parity(kmeans, X, init, r, k)
+    check_certificate(X, init, r["assign"], r["prices"])
