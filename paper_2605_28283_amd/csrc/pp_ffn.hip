@@ -485,6 +485,18 @@ __device__ __forceinline__ void rows_read(RowTile &t, const DownRowsLds &S, int 
     t.off = *reinterpret_cast<const int4 *>(&S.off[slot][4 * (lane >> 4)]);
 }
 
+// The barrier after which tile k + 1 is in its slot and the carrying wavefronts
+// may write to tile k's.  This wavefront has then read all of tile k (t): the
+// barrier takes what it read as operands, so that the compiler waits for those
+// reads, and for no later access.
+__device__ __forceinline__ void rows_handover(const RowTile &t) {
+    auto v = [](const uint4 &u) { return __builtin_bit_cast(u32x4_t, u); };
+    asm volatile("s_barrier" ::"v"(v(t.hi[0])), "v"(v(t.lo[0])), "v"(v(t.hi[1])), "v"(v(t.lo[1])),
+                 "v"(v(t.hi[2])), "v"(v(t.lo[2])), "v"(v(t.hi[3])), "v"(v(t.lo[3])),
+                 "v"(__builtin_bit_cast(u32x4_t, t.off))
+                 : "memory");
+}
+
 // A tile's products on their way to the LDS outputs.
 struct RowSums {
     f32x4 a0, a1;
@@ -518,10 +530,7 @@ __device__ __forceinline__ void rows_step(const DownRowsLds &S, char *yb, const 
         const int s = j >> 2;
         a[j & 1] = mfma16((j & 2) ? cur.lo[s] : cur.hi[s], W[4 * (j & 1) + s], a[j & 1]);
         if (j < 4) y[j] = sums_load(yb, prev, j);
-        // Tile k + 1 is in its slot, and this wavefront has read all of tile k:
-        // LDS accesses end in order, and eight of y were issued after those
-        // reads (tile 0's were waited for), of which six may be in flight.
-        if (j == 5) asm volatile("s_waitcnt lgkmcnt(6)\n\ts_barrier" ::: "memory");
+        if (j == 5) rows_handover(cur);
         if (j >= 6 && j < 10) {
             nxt.hi[j - 6] = rows_frag(S.h[slot][0], j - 6, lane);
             nxt.lo[j - 6] = rows_frag(S.h[slot][1], j - 6, lane);
@@ -617,8 +626,6 @@ __device__ __forceinline__ void rows_multiply(const DownRowsLds &S, char *yb, co
     __syncthreads();  // tile 0 is in its slot
     RowTile A, B;
     rows_read(A, S, 0, lane);
-    // the first step has no sums to store between these reads and its barrier
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     RowSums prev;
     prev.a0 = prev.a1 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
