@@ -431,15 +431,16 @@ __global__ __launch_bounds__(256) void dispatch_k(const uint32_t *__restrict__ s
 //
 // What bounds it: the CU's LDS accesses (per step 32 KiB of h read by the four
 // wavefronts, 8 KiB read and written of y, 8 KiB of h written: about 480
-// cycles of 650; the products take 300, and without the weight loads a step
-// is a fifth shorter).  A block of 64 rows by 512 tokens, staged in LDS and
+// cycles of 600 to 650; the products take 300, and without the weight loads a
+// step is a tenth to a sixth shorter).  A block of 64 rows by 512 tokens, staged in LDS and
 // multiplied by whichever wavefronts the run's tiles fill, with two barriers
 // per expert, took (LLaMA-3-8B shape) 132 us for 2048 tokens at tau 0.7 and
-// 1550 us for 16384 at tau 0.9; this takes 95 and 1080 (98 and 1150 with h
+// 1550 us for 16384 at tau 0.9; this takes 88 and 1070 (98 and 1150 with h
 // carried as 64-byte pieces of sixteen rows).  For 777 tokens of a 1024-wide
-// GELU layer (16-row blocks before): 51 and 23.
+// GELU layer (16-row blocks before): 51 and 21.
 constexpr int kTileAhead = 8;      // tiles in flight per carrying wavefront
-constexpr int kWAhead = 2;         // experts whose down rows are loaded ahead
+constexpr int kWAhead = 2;         // experts whose down rows are loaded ahead (2048 tokens at
+                                   // tau 0.7, LLaMA-3-8B shape: 1 95 us, 2 88, 3 90)
 constexpr int kRowThreads = 512;
 static_assert(kTileAhead % 2 == 0, "tile k lies in slot k % 2");
 
@@ -551,11 +552,12 @@ __device__ __forceinline__ void rows_step(const DownRowsLds &S, char *yb, const 
 // One expert's run of `tiles` tiles on a multiplying wavefront; k: index of
 // its first tile, whose fragments are in A; leaves the next run's first tile
 // in A.  Loads a coming expert's down rows into Wn on the way.
+template <bool LOAD>
 __device__ __forceinline__ void rows_expert(const DownRowsLds &S, char *yb, RowTile &A, RowTile &B,
                                             RowSums &prev, int k, int tiles, const uint4 (&W)[8],
                                             int col, int lane, uint4 (&Wn)[8],
                                             const uint16_t *wn) {
-    rows_step<true>(S, yb, A, B, prev, (k + 1) & 1, W, col, lane, Wn, wn);
+    rows_step<LOAD>(S, yb, A, B, prev, (k + 1) & 1, W, col, lane, Wn, wn);
     for (; tiles > 2; tiles -= 2) {
         rows_step<false>(S, yb, B, A, prev, k & 1, W, col, lane, Wn, wn);
         rows_step<false>(S, yb, A, B, prev, (k + 1) & 1, W, col, lane, Wn, wn);
@@ -605,9 +607,12 @@ __device__ __forceinline__ void rows_place(int unit, int nRB, int nC, int &rb, i
     rb = g * kRowGroup + r - c * w;
 }
 
-// A multiplying wavefront's unit of m experts.  The loop ends by returning, so
-// that no path joins the loads in flight at its head and each wait covers one
-// expert's loads only.
+// A multiplying wavefront's unit of m experts, in whole rings and what is left:
+// with the loop's only exit at its bottom, every wait covers the loads of the
+// expert that is multiplied and leaves the next one's in flight (an exit inside
+// the ring joined the loop head with fewer loads in flight, and the first
+// expert of every ring waited for both: 95 us for 2048 tokens of the shape
+// above, 88 so).
 __device__ __forceinline__ void rows_multiply(const DownRowsLds &S, char *yb, const DNParams &P,
                                               int C, int rb, int m, int wv, int lane) {
     constexpr int kRing = kWAhead + 1;
@@ -630,23 +635,29 @@ __device__ __forceinline__ void rows_multiply(const DownRowsLds &S, char *yb, co
     prev.a0 = prev.a1 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < 4; ++i) prev.off[i] = row_off(C) + col;
-    int k = 0;
-    for (int x0 = 0;; x0 += kRing) {
+    int k = 0, x = 0;
+    for (; x + kRing <= m; x += kRing) {
 #pragma unroll
         for (int i = 0; i < kRing; ++i) {
-            if (x0 + i >= m) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) sums_store(yb, sums_load(yb, prev, j), prev, j);
-                // the carrying wavefronts end on a whole ring
-                for (; k % kTileAhead != 0; ++k) __syncthreads();
-                return;
-            }
-            const int tiles = ent(x0 + i) >> 8;
-            rows_expert(S, yb, A, B, prev, k, tiles, W[i], col, lane, W[(i + kWAhead) % kRing],
-                        wd + (size_t)(ent(x0 + i + kWAhead) & 255) * estride);
+            const int tiles = ent(x + i) >> 8;
+            rows_expert<true>(S, yb, A, B, prev, k, tiles, W[i], col, lane, W[(i + kWAhead) % kRing],
+                              wd + (size_t)(ent(x + i + kWAhead) & 255) * estride);
             k += tiles;
         }
     }
+    // the experts past the last whole ring, whose down rows it has loaded
+#pragma unroll
+    for (int i = 0; i < kWAhead; ++i) {
+        if (x + i < m) {
+            const int tiles = ent(x + i) >> 8;
+            rows_expert<false>(S, yb, A, B, prev, k, tiles, W[i], col, lane, W[i], wd);
+            k += tiles;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sums_store(yb, sums_load(yb, prev, j), prev, j);
+    // the carrying wavefronts end on a whole ring
+    for (; k % kTileAhead != 0; ++k) __syncthreads();
 }
 
 // A carrying wavefront's unit (p: which of the four), in whole rings of tiles

@@ -63,3 +63,16 @@ def test_prefill_longest_tile_list():
     finally:
         pp.prunepath_destroy(h)
     assert ((ys[0] - ys[1]).norm() / ys[1].norm()).item() <= 1e-5
+
+
+@pytest.mark.parametrize("E", [1, 2, 3, 4, 5, 6, 7])
+def test_prefill_expert_rings(oracle_mod, E):
+    """Units of one expert to seven, each with one tile and with three (the last
+    of two tokens): rings of three experts, and none, one or two after them."""
+    d = 128
+    L = make_layer(d, E * 128, E, 720 + E)
+    for T in (9, 34):
+        x, _ = make_tokens(T, d, 730 + T)
+        with DevLayer(L, T) as dl:
+            print("prefill rings E=%d T=%d" % (E, T), flush=True)
+            parity(oracle_mod, dl, "prefill", x, 1.0)
