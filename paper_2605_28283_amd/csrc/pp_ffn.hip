@@ -392,11 +392,7 @@ __global__ __launch_bounds__(256) void dispatch_k(const uint32_t *__restrict__ s
     const int nch = (c + gs - 1) / gs;
     int cb, off, nG, npairs;
     block_excl_scan2(nch, c, &cb, &off, &nG, &npairs, scan);
-    if (tid < E) {
-        plan.egrp[tid] = cb;
-        ebase[tid] = off;
-    }
-    if (tid == 0) plan.egrp[E] = nG;
+    if (tid < E) ebase[tid] = off;
     const int gbase = nch > 0 ? c / nch : 0, grem = nch > 0 ? c - gbase * nch : 0;
     for (int ch = 0, first = 0; ch < nch; ++ch) {
         const int g = cb + ch, n = gbase + (ch < grem ? 1 : 0);
@@ -462,7 +458,7 @@ struct DownRowsLds {
     // the products of empty tile places
 };
 static_assert(sizeof(DownRowsLds) % 16 == 0, "y rows are read as float4");
-static_assert(sizeof(DownRowsLds) <= kRowLdsFixed, "pf_max_chunk counts on it");
+static_assert(sizeof(DownRowsLds) == kRowLdsFixed, "pf_row_lds counts on it");
 
 // A tile's fragments as held by a multiplying wavefront.
 struct RowTile {

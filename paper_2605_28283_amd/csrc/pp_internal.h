@@ -37,8 +37,8 @@ struct profiler;  // per-kernel event timing (benchmarking aid)
 
 // Work plan of one FFN call (device memory): head[0] = number of groups,
 // head[1] = number of (token, expert) pair rows; group g is expert grp_e[g]
-// with grp_n[g] <= 64 tokens toklist[grp_tok[g] .. + grp_n[g]) whose h rows
-// start at grp_pair[g].
+// with grp_n[g] <= 64 (prefill: 128) tokens toklist[grp_tok[g] .. + grp_n[g])
+// whose h rows start at grp_pair[g].
 struct PlanView {
     int32_t *head;
     int32_t *grp_e;
@@ -46,7 +46,6 @@ struct PlanView {
     int32_t *grp_n;
     int32_t *grp_tok;
     int32_t *toklist;
-    int32_t *egrp;  // prefill: expert e owns groups [egrp[e], egrp[e + 1])
 };
 
 // Work-unit order for persistent grids whose size is a multiple of 8: the
@@ -145,7 +144,7 @@ struct pp_layer {
     int32_t *tokl;      // [E][max_tokens] token ids per expert (prefill)
     int32_t *pf_cut;    // prefill: [E][chunks + 1] bucket position where each token chunk starts
     int32_t *pf_ebase;  // prefill: [E] first pair row of each expert's bucket
-    int32_t *plan;      // PlanView storage: 4 + 4 * plan_max_groups + E + 1 ints
+    int32_t *plan;      // PlanView storage: 4 + 4 * plan_max_groups ints
     int32_t *dec_tok;   // [64 * E] token ids of the decode plan, pair order
     unsigned long long *emask;  // [E] decode: tokens that kept each expert (zero between calls)
     pp::profiler *prof; // non-NULL while per-kernel timing is recorded
@@ -204,7 +203,6 @@ inline PlanView plan_view(pp_layer *L, bool prefill) {
     v.grp_n = v.grp_pair + G;
     v.grp_tok = v.grp_n + G;
     v.toklist = prefill ? L->tokl : L->dec_tok;
-    v.egrp = v.grp_tok + G;
     return v;
 }
 
