@@ -53,10 +53,12 @@ struct DNParams {
 // other, and one barrier per sub-chunk.  Token tiles are multiplied in
 // pairs, the pairs past the group skipped.  One workgroup per CU; the groups
 // of one expert are neighbouring units on one XCD, where they share the
-// expert's weights in L2.  What bounds it is the CUs' reads from L2: 16384
-// tokens at tau 0.9 on the LLaMA-3-8B shape take 605 us with 8.3 GB requested
-// (13.8 TB/s; leaving the products out saved 7 %), 700 us when a copy took
-// 64-byte pieces of rows.
+// expert's weights in L2.  16384 tokens at tau 0.9 on the LLaMA-3-8B shape take
+// 605 us with 8.3 GB requested of L2 (13.8 TB/s, half of what plain reads reach
+// with more bytes in flight per CU), 700 us when a copy took 64-byte pieces of
+// rows.  Left out one at a time, the token copies save 28 %, the weight loads
+// 12 %, the products 7 % and the LDS reads nothing: waits for the copies weigh
+// most, and no unit is at its rate.
 constexpr int kPfXC = 8;                         // K-steps per staged token sub-chunk
 constexpr int kPfPF = 4;                         // K-steps of weights in flight per wavefront
 constexpr int kPfNT = kPfGroupTokens / 16;       // token tiles per group
@@ -428,7 +430,7 @@ __global__ __launch_bounds__(256) void dispatch_k(const uint32_t *__restrict__ s
 // What bounds it: the CU's LDS accesses (per step 32 KiB of h read by the four
 // wavefronts, 8 KiB read and written of y, 8 KiB of h written: about 480
 // cycles of 600 to 650; the products take 300, and without the weight loads a
-// step is a tenth to a sixth shorter).  A block of 64 rows by 512 tokens, staged in LDS and
+// step is a tenth to a fifth shorter).  A block of 64 rows by 512 tokens, staged in LDS and
 // multiplied by whichever wavefronts the run's tiles fill, with two barriers
 // per expert, took (LLaMA-3-8B shape) 132 us for 2048 tokens at tau 0.7 and
 // 1550 us for 16384 at tau 0.9; this takes 88 and 1070 (98 and 1150 with h

@@ -1,8 +1,10 @@
-"""Balanced k-means where its auction and distance kernels change path: more
-rows than a price workgroup gathers at once, one cluster holding more rows
-than fit its LDS list, cluster counts that do not divide over the bid
-wavefronts or fill a distance tile, and the largest number of tiles.  Checked
-by the duality certificate (test_gpu_kmeans.py), exact balance and Pi."""
+"""Balanced k-means where its kernels change path: more rows than a price
+workgroup gathers at once, one cluster holding more rows than fit its LDS
+list, cluster counts that do not divide over the bid wavefronts or fill a
+distance tile, the largest number of tiles, and the shortest-path finish with
+its edge costs in LDS and in memory; features that are not finite and rows of
+unequal norm.  Checked by the duality certificate (test_gpu_kmeans.py), exact
+balance and Pi."""
 import numpy as np
 import pytest
 
